@@ -3,10 +3,12 @@
 import os
 import subprocess
 import sys
+from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
-SRC = os.path.join(HERE, "csrc", "asymspec.hip")
+CSRC = os.path.join(HERE, "csrc")
+OBJ = os.path.join(HERE, "build")
 INC = os.path.join(ROOT, "include")
 OUT = os.path.join(HERE, "libasymspec.so")
 # per-kernel register and scratch use reported by the compiler for the last
@@ -15,7 +17,7 @@ RESOURCES = os.path.join(HERE, "libasymspec.resources.txt")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 FLAGS = [
-    "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
+    "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
     # keep the compiler from emitting packed-FP32 VALU ops
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-ffp-contract=off",
@@ -23,23 +25,49 @@ FLAGS = [
 ]
 
 
-def build(verbose: bool = False, extra=()) -> str:
-    tmp = OUT + ".tmp"
-    cmd = [HIPCC, *FLAGS, "-Rpass-analysis=kernel-resource-usage", "-fno-caret-diagnostics", *extra, "-I", INC, SRC, "-o", tmp]
-    if verbose:
-        print(" ".join(cmd), flush=True)
+def units():
+    """(object name, source, defines) of every object of the library: the host
+    side, and one object per instance of the decision kernel (storage type x
+    source of delta x variant), compiled in parallel."""
+    out = [("asymspec", "asymspec.hip", [])]
+    for dt in (0, 1):
+        for dm in (0, 1, 2):
+            for var in (0, 1, 2):
+                out.append((f"fv_{dt}{dm}{var}", "kernels.hip",
+                            [f"-DASYMSPEC_PART_DT={dt}", f"-DASYMSPEC_PART_DM={dm}", f"-DASYMSPEC_PART_VAR={var}"]))
+    return out
+
+
+def _run(cmd):
     r = subprocess.run(cmd, capture_output=True, text=True)
     lines = (r.stdout + r.stderr).splitlines()
     usage = [l for l in lines if "kernel-resource-usage" in l]
     msg = "\n".join(l for l in lines if "packed-fp32-ops" not in l and "unknown target feature" not in l
                     and "kernel-resource-usage" not in l)
     if r.returncode != 0:
-        raise RuntimeError(f"hipcc failed ({r.returncode}):\n{msg}")
-    if verbose and msg.strip():
-        print(msg)
+        raise RuntimeError(f"hipcc failed ({r.returncode}): {' '.join(cmd)}\n{msg}")
+    return usage, msg
+
+
+def build(verbose: bool = False, extra=()) -> str:
+    os.makedirs(OBJ, exist_ok=True)
+
+    def compile_one(unit):
+        name, src, defs = unit
+        obj = os.path.join(OBJ, name + ".o")
+        return obj, *_run([HIPCC, *FLAGS, "-c", "-Rpass-analysis=kernel-resource-usage",
+                           "-fno-caret-diagnostics", *defs, *extra, "-I", INC, os.path.join(CSRC, src), "-o", obj])
+
+    jobs = int(os.environ.get("MAX_JOBS", 0)) or len(os.sched_getaffinity(0))
+    with ThreadPoolExecutor(max(1, min(jobs, 16))) as pool:
+        done = list(pool.map(compile_one, units()))
+    tmp = OUT + ".tmp"
+    _run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", *(d[0] for d in done), "-o", tmp])
+    if verbose:
+        print("\n".join(d[2] for d in done if d[2].strip()))
     os.replace(tmp, OUT)
     with open(RESOURCES, "w") as f:
-        f.write(resource_report(usage))
+        f.write(resource_report([l for d in done for l in d[1]]))
     return OUT
 
 
@@ -85,7 +113,7 @@ PROBE = os.path.join(HERE, "libasymspec_probe.so")
 def build_probe(verbose: bool = False) -> str:
     """libasymspec_probe.so: the read-ceiling probe (not the decision step)."""
     tmp = PROBE + ".tmp"
-    cmd = [HIPCC, *FLAGS, "-I", INC, PROBE_SRC, "-o", tmp]
+    cmd = [HIPCC, *FLAGS, "-shared", "-I", INC, PROBE_SRC, "-o", tmp]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"probe build failed ({r.returncode}):\n{r.stdout}{r.stderr}")
