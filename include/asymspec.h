@@ -220,11 +220,10 @@ int asymspec_fuse_verify(const void* verifier_logits,
  * tokens outside the set masked in all three views: f(x) = t(x) + beta delta
  * (vocab_map[x]), the log-softmaxes of Eq. 3-4 (so D and p_b), the sampling
  * target and proposal, the emission and the bonus token.  Drafter tokens
- * that no verifier token maps to are never read.  A draft outside the set has
- * no mass in any view and is rejected.  The drafter rows are gathered element
- * by element (a map is in general no permutation of contiguous runs); when
- * no two verifier tokens share a drafter id, rows with no argmax to find read
- * the drafter rows in their own order and gather t instead.
+ * that no verifier token maps to contribute nothing, whatever they hold.  A
+ * draft outside the set has no mass in any view and is rejected.  The drafter
+ * rows are read contiguously, tile by tile, and the mapped pairs taken from
+ * LDS; the call enqueues a short sequence of kernels.
  */
 /* Workspace bytes of asymspec_fuse_verify_xvocab (0 for invalid arguments). */
 size_t asymspec_workspace_size_xvocab(int B, int K, int V, int Vd, int dtype);

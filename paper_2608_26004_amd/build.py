@@ -27,10 +27,12 @@ FLAGS = [
 
 def units():
     """(object name, source, defines) of every object of the library: the host
-    side, and one object per instance of the decision kernel (storage type x
-    source of delta x variant), compiled in parallel."""
+    side, the cross-family kernels per storage type, and one object per
+    instance of the decision kernel (storage type x source of delta x variant),
+    compiled in parallel."""
     out = [("asymspec", "asymspec.hip", [])]
     for dt in (0, 1):
+        out.append((f"xv_{dt}", "xvocab.hip", [f"-DASYMSPEC_PART_DT={dt}"]))
         for dm in (0, 1, 2):
             for var in (0, 1, 2):
                 out.append((f"fv_{dt}{dm}{var}", "kernels.hip",

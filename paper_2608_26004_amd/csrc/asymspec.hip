@@ -38,22 +38,9 @@
 #include "dump.h"
 #include "kernels.h"
 #include "schedule.h"
+#include "xvocab_host.h"
 
 namespace asym {
-
-// The drafter-to-verifier map of a cross-family call: inv[j] = x for the
-// verifier token x with vmap[x] = j, else -1; inv[Vd] is set when two
-// verifier tokens name the same drafter id (the map is then not used).
-__global__ void inv_clear_kernel(int32_t* inv, int Vd) {
-  for (int j = blockIdx.x * blockDim.x + threadIdx.x; j <= Vd; j += gridDim.x * blockDim.x)
-    inv[j] = j < Vd ? -1 : 0;
-}
-__global__ void inv_fill_kernel(const int32_t* vmap, int V, int32_t* inv, int Vd) {
-  for (int x = blockIdx.x * blockDim.x + threadIdx.x; x < V; x += gridDim.x * blockDim.x) {
-    const int j = vmap[x];
-    if (j >= 0 && j < Vd && atomicCAS(&inv[j], -1, x) != -1) inv[Vd] = 1;
-  }
-}
 
 __global__ void fill_zero_kernel(uint32_t* p, size_t n) {
   for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x)
@@ -64,14 +51,15 @@ __global__ void fill_zero_kernel(uint32_t* p, size_t n) {
 struct Layout {
   int S, VE;
   size_t rows;
-  size_t off_rec1, off_dec, off_rec2, off_err, off_inv, off_trace, total;
+  size_t off_rec1, off_dec, off_rec2, off_err, off_xv, off_trace, total;
+  XLayout xv;
 };
 
 static size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 // Vd > 0: a drafter vocabulary of Vd tokens (cross-family calls); rows then
 // have as many chunks as the longer of the two vocabularies needs, and the
-// workspace holds the drafter-to-verifier map.
+// tile lists and pass-2 sums of xvocab.h take the place of rec2.
 static bool make_layout(int B, int K, int V, int dtype, Layout& L, int Vd = 0) {
   if (B < 1 || K < 0 || K > kMaxK || V < 1 || Vd < 0) return false;
   if (dtype != ASYMSPEC_BF16 && dtype != ASYMSPEC_FP32) return false;
@@ -91,9 +79,14 @@ static bool make_layout(int B, int K, int V, int dtype, Layout& L, int Vd = 0) {
   L.off_err = off;  off = align_up(off + 8, 256);
   L.off_rec1 = off; off = align_up(off + L.rows * L.S * kR1 * 8, 256);
   L.off_dec = off;  off = align_up(off + (size_t)B * (kDecHdr + (size_t)(K + 1) * kDecRow) * 8, 256);
-  L.off_rec2 = off; off = align_up(off + L.rows * L.S * kR2 * 8, 256);
-  // cross-family: inverse map [Vd] and its duplicate flag
-  L.off_inv = off;  off = align_up(off + (Vd > 0 ? (size_t)Vd * 4 + 4 : 0), 256);
+  L.off_rec2 = L.off_xv = off;
+  off = align_up(off + L.rows * L.S * kR2 * 8, 256);
+  if (Vd > 0) {
+    // (never less than a same-vocabulary call of the shape needs, plus Vd ids)
+    const size_t n = dtype == ASYMSPEC_BF16 ? xv_layout<ASYMSPEC_BF16>(B, K, V, Vd, L.xv)
+                                            : xv_layout<ASYMSPEC_FP32>(B, K, V, Vd, L.xv);
+    off = std::max(align_up(off + (size_t)Vd * 4 + 4, 256), L.off_xv + n);
+  }
 #ifdef ASYMSPEC_TRACE
   // 32 bytes per work item, for at most (K + 1 + kMaxP2) S + 3 items per
   // request (statistics, pass 2, decide, pick, verdict)
@@ -103,10 +96,10 @@ static bool make_layout(int B, int K, int V, int dtype, Layout& L, int Vd = 0) {
   return true;
 }
 
-// Through a vocabulary map every chunk of a row gathers from the whole of
-// the row's drafter logits; launched with this much unused dynamic LDS per
-// workgroup, fewer workgroups share a CU, so each XCD works on fewer rows at
-// a time and its L2 keeps their drafter rows.
+// Full log-probability rows through a vocabulary map: every chunk of a row
+// gathers from the whole of the row's drafter logits; launched with this much
+// unused dynamic LDS per workgroup, fewer workgroups share a CU, so each XCD
+// works on fewer rows at a time and its L2 keeps their drafter rows.
 #ifndef ASYMSPEC_XV_LDS
 #define ASYMSPEC_XV_LDS 49152
 #endif
@@ -116,7 +109,6 @@ struct DevInfo {
   int ok = 0;
   int n_cu = 0;
   int max_blocks[2] = {0, 0};   // co-resident workgroups, per dtype
-  int max_blocks_xv[2] = {0, 0};   // the same with kXvLds of dynamic LDS
 };
 
 static DevInfo g_dev[64];
@@ -164,20 +156,16 @@ static const DevInfo* device_info() {
   if (std::strncmp(pr.gcnArchName, "gfx950", 6) != 0) return nullptr;
   di.n_cu = pr.multiProcessorCount;
   for (int dt = 0; dt < 2; ++dt) {
-    int nb = 1 << 30, nx = 1 << 30;
+    int nb = 1 << 30;
     for (int v = 0; v < 3; ++v)
       for (int dm = 0; dm < 3; ++dm) {
-        int x = 0, y = 0;
+        int x = 0;
         const void* k = kernel_ptr(dt, v == 0, dm, v == 2);
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&x, k, kThreads, 0) != hipSuccess ||
-            hipOccupancyMaxActiveBlocksPerMultiprocessor(&y, k, kThreads, kXvLds) != hipSuccess)
-          return nullptr;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&x, k, kThreads, 0) != hipSuccess) return nullptr;
         nb = std::min(nb, x);
-        nx = std::min(nx, y);
       }
-    if (nb < 1 || nx < 1) return nullptr;
+    if (nb < 1) return nullptr;
     di.max_blocks[dt] = nb * di.n_cu;
-    di.max_blocks_xv[dt] = nx * di.n_cu;
   }
   di.ok = 1;
   return &di;
@@ -322,7 +310,6 @@ static int fuse_verify_impl(const void* t, const void* a, const void* b, int dty
   A.fuse_bonus = fb ? 1 : 0;
   A.vmap = vmap;
   A.Vd = vmap != nullptr ? Vd : V;
-  A.inv = vmap != nullptr ? (const int32_t*)(ws + L.off_inv) : nullptr;
 #ifdef ASYMSPEC_TRACE
   A.trace = (uint64_t*)(ws + L.off_trace);
   A.trace_items = (unsigned)((size_t)B * ((size_t)(K + 1 + kMaxP2) * L.S + 3));
@@ -333,7 +320,7 @@ static int fuse_verify_impl(const void* t, const void* a, const void* b, int dty
   A.poll_ticks = g_poll_ticks.load();
   // lags scale with the number of workgroups the chip holds at once
   const int ee_rows = ee ? (params->early_rows > 0 ? params->early_rows : 2) : 0;
-  const int in_flight = vmap != nullptr ? di->max_blocks_xv[dtype] : di->max_blocks[dtype];
+  const int in_flight = di->max_blocks[dtype];
   // pass 2 in 8, 4 or 2 items per chunk while that many still fit on the
   // chip at once: a small batch leaves most of it idle, and pass 2's
   // divergence terms are arithmetic-bound within one workgroup
@@ -358,20 +345,15 @@ static int fuse_verify_impl(const void* t, const void* a, const void* b, int dty
   if (fused_logprobs_full != nullptr && nblk > 0x7FFFFFFFull) return ASYMSPEC_E_ARG;
   hipError_t e = hipSuccess;
   if (vmap != nullptr) {
-    // the drafter-to-verifier map, rebuilt for every call (the caller's map
-    // may change between calls)
-    int32_t* inv = (int32_t*)(ws + L.off_inv);
-    const int nb_d = (int)std::min<long long>((Vd + 1 + 255) / 256, 4096);
-    const int nb_v = (int)std::min<long long>((V + 255) / 256, 4096);
-    hipLaunchKernelGGL(inv_clear_kernel, dim3(nb_d), dim3(256), 0, (hipStream_t)stream, inv, Vd);
-    hipLaunchKernelGGL(inv_fill_kernel, dim3(nb_v), dim3(256), 0, (hipStream_t)stream, vmap, V, inv, Vd);
-    e = hipGetLastError();
-    if (e != hipSuccess) return ASYMSPEC_E_DEVICE;
+    e = dtype == ASYMSPEC_BF16
+            ? xv_launch<ASYMSPEC_BF16>(A, L.xv, ws + L.off_xv, ee_rows, di->n_cu, (hipStream_t)stream)
+            : xv_launch<ASYMSPEC_FP32>(A, L.xv, ws + L.off_xv, ee_rows, di->n_cu, (hipStream_t)stream);
+  } else {
+    void* args[] = {&A};
+    e = hipLaunchKernel(kernel_ptr(dtype, params->beta == 1.0f, params->delta_mode,
+                                   params->gate_mode == ASYMSPEC_GATE_KL), dim3(grid),
+                                   dim3(kThreads), args, 0, (hipStream_t)stream);
   }
-  void* args[] = {&A};
-  e = hipLaunchKernel(kernel_ptr(dtype, params->beta == 1.0f, params->delta_mode,
-                                 params->gate_mode == ASYMSPEC_GATE_KL), dim3(grid),
-                                 dim3(kThreads), args, vmap != nullptr ? kXvLds : 0, (hipStream_t)stream);
   if (e == hipSuccess && fused_logprobs_full != nullptr) {
     // one workgroup per (row, chunk), after the decision kernel on the stream
     float* full = fused_logprobs_full;

@@ -32,23 +32,11 @@ DEV void stats_chunk(const KArgs& A, int req, int i, int m, Smem& sm) {
   }
 }
 
-// Workgroups go to the 8 XCDs in turn, so consecutive items of a request
-// sit on different XCDs.  Through a vocabulary map every chunk of a row
-// gathers from the whole of the row's drafter logits; the items of a request
-// are then renumbered so that those sharing an XCD take consecutive chunks
-// of the same rows, and each XCD's L2 holds few drafter rows at a time.
 template <int DT, bool kB1, int DM, bool kKL>
 DEV void stats_dispatch(const KArgs& A, int req, int sub, Smem& sm) {
-  int p = sub;
-  if (A.vmap != nullptr) {
-    // within each group of rows (all rows, or the two groups of early exit)
-    const int n1 = A.sc.G * A.S, n = (A.K + 1) * A.S;
-    p = sub < n1 ? xcd_grouped(sub, n1) : n1 + xcd_grouped(sub - n1, n - n1);
-  }
-  const int i = p / A.S, m = p - i * A.S;
+  const int i = sub / A.S, m = sub - i * A.S;
   stats_chunk<DT, kB1, DM, kKL>(A, req, i, m, sm);
 }
-
 
 #ifndef ASYMSPEC_WAVES
 #define ASYMSPEC_WAVES 4

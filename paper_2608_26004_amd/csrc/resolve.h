@@ -546,9 +546,7 @@ DEV void pass2_sums(const KArgs& A, const RowGeo& g, long long rel0, int nk, boo
         if (kNb) mask_vec<DT>(A, g, vi, vb[k]);
       } else if (kMode == 2) {
         if (nt) fix_vec<DT>(A, g, A.t, vi, vt[k]);
-        if (A.vmap != nullptr) {
-          map_vecs<DT>(A, g, vi, vt[k], va[k], vb[k], nab);
-        } else if (nab) {
+        if (nab) {
           fix_vec<DT>(A, g, A.a, vi, va[k]);
           if (kNb) fix_vec<DT>(A, g, A.b, vi, vb[k]);
         }
@@ -595,7 +593,7 @@ DEV void pass2_sums_any(const KArgs& A, const RowGeo& g, long long rel0, int nk,
                         bool dj, bool dr, bool db, const ResidConst& rk, const JsdConst& jk, float& accj,
                         float (&seg)[kSegPerLane]) {
   constexpr int VE = Elem<DT>::VE;
-  if (A.vmap != nullptr || has_tail(A, c0, c1))
+  if (has_tail(A, c0, c1))
     pass2_sums<DT, 2, DM, kNb>(A, g, rel0, nk, dj, dr, db, rk, jk, accj, seg);
   else if (dr && !dj && !db && c0 * VE >= g.e0 && c1 * VE <= g.e0 + A.V)
     pass2_sums<DT, 0, DM, kNb, true, kGF>(A, g, rel0, nk, dj, dr, db, rk, jk, accj, seg);
@@ -635,7 +633,7 @@ DEV void pass2_item(const KArgs& A, int req, int sub, Smem& sm) {
     for (int k = 0; k < kSegPerLane; ++k) seg[k] = 0.0f;
     if (task != 0) {
       // a row with a == b bitwise has no divergence task and skips b
-      const bool nbr = (cst[D_STATUS] & kStNeq) != 0u || A.vmap != nullptr;
+      const bool nbr = (cst[D_STATUS] & kStNeq) != 0u;
       if (nk >= 4) {
         if (nbr) pass2_sums_any<DT, DM, true, 4>(A, g, rel0, nk, c0, c1, dj, dr, db, rk, jk, accj, seg);
         else pass2_sums_any<DT, DM, false, 4>(A, g, rel0, nk, c0, c1, dj, dr, db, rk, jk, accj, seg);
@@ -677,6 +675,28 @@ DEV void pass2_item(const KArgs& A, int req, int sub, Smem& sm) {
 // Sub-block sums a lane of the pick holds at once.
 constexpr int kPickRun = 8;
 
+// Where a cross-family call's pass-2 kernel left its sums: [rows][T][nsub]
+// weight sums and [rows][T] divergence partials, T tiles per row, written by
+// an earlier kernel (no tags); a sub-block is kXSub consecutive tokens.
+struct XPass2 { const float* sums; const float* jpart; int T, nsub; };
+
+// The sums of sub-blocks [s0, s0 + n) of row `row` of a cross-family call,
+// each over the row's tiles in order; the other entries of v are zero.
+DEV void load_sub_tiles(const XPass2& xp, size_t row, int s0, int n, float (&v)[kPickRun]) {
+  #pragma unroll
+  for (int j = 0; j < kPickRun; ++j) v[j] = 0.0f;
+  // (a lane without sub-blocks reads the row's first and drops them)
+  const float* p = xp.sums + row * xp.T * xp.nsub;
+  #pragma unroll 4
+  for (int t = 0; t < xp.T; ++t) {
+    #pragma unroll
+    for (int j = 0; j < kPickRun; ++j) {
+      const float x = p[(size_t)t * xp.nsub + (j < n ? s0 + j : 0)];
+      v[j] += j < n ? x : 0.0f;
+    }
+  }
+}
+
 // The tagged slots of sub-blocks [s0, s0 + n) (n <= kPickRun) of pass-2
 // record area rec, requested at once and polled until all are in (bounded;
 // ok cleared on a timeout); the other entries of v are zero.
@@ -712,13 +732,15 @@ DEV void load_sub_run(const KArgs& A, const uint64_t* rec, int s0, int n, float 
 // weight; otherwise the element's index, and, when the scan itself found it,
 // sm.flags[2] = 1 and its logit (f for drafts, t for the bonus row) in
 // sm.dd[3].  Whole workgroup.
-template <int DT, int DM>
-DEV int cdf_pick(const KArgs& A, int req, int i, double u, bool bonus, Smem& sm, bool& ok) {
-  constexpr int VE = Elem<DT>::VE;
+// kXv: a cross-family call, whose sub-blocks are 512 consecutive verifier
+// tokens, 8 per lane, gathered through the map.
+template <int DT, int DM, bool kXv>
+DEV int cdf_pick(const KArgs& A, int req, int i, double u, bool bonus, Smem& sm, bool& ok, const XPass2& xp) {
+  constexpr int VE = kXv ? 8 : Elem<DT>::VE;
   const int lane = lane_id(), w = wave_id();
   if (w == 0) {
     const RowGeo g = row_span<DT>(A, req * (A.K + 1) + i);
-    const int nsub = A.S * kSubPerChunk;
+    const int nsub = kXv ? xp.nsub : A.S * kSubPerChunk;
     // lane l holds sub-blocks [l * per, l * per + per) in runs of kPickRun
     const int per = (nsub + 63) / 64;
     const int nrun = (per + kPickRun - 1) / kPickRun;
@@ -726,9 +748,13 @@ DEV int cdf_pick(const KArgs& A, int req, int i, double u, bool bonus, Smem& sm,
     const uint64_t* rec = p2_rec(A, req, i, 0);
     float v[kPickRun];
     double lsum = 0.0;
+    auto load_run = [&](int a, int n) {
+      if (kXv) load_sub_tiles(xp, (size_t)g.row, a, n, v);
+      else load_sub_run(A, rec, a, n, v, ok);
+    };
     for (int q = 0; q < nrun; ++q) {
       const int a = min(s0 + q * kPickRun, s1);
-      load_sub_run(A, rec, a, min(kPickRun, s1 - a), v, ok);
+      load_run(a, min(kPickRun, s1 - a));
       #pragma unroll
       for (int j = 0; j < kPickRun; ++j) lsum += (double)v[j];
     }
@@ -749,7 +775,7 @@ DEV int cdf_pick(const KArgs& A, int req, int i, double u, bool bonus, Smem& sm,
         double run = excl;
         for (int q = 0; q < nrun; ++q) {
           const int a = min(s0 + q * kPickRun, s1);
-          if (nrun > 1) load_sub_run(A, rec, a, min(kPickRun, s1 - a), v, ok);
+          if (nrun > 1) load_run(a, min(kPickRun, s1 - a));
           #pragma unroll
           for (int j = 0; j < kPickRun; ++j) {
             const double nx = run + (double)v[j];
@@ -772,41 +798,61 @@ DEV int cdf_pick(const KArgs& A, int req, int i, double u, bool bonus, Smem& sm,
       }
       if (sel >= 0) {
         // lane l scans vector l of the sub-block
-        const int ch = sel / kSubPerChunk, sub = sel % kSubPerChunk;
-        const long long sv0 = g.vbeg + (long long)ch * kChunkVec + (long long)sub * 64;
-        const long long vi = sv0 + lane;
         const uint32_t* cst = sm.rows[i];
         const ResidConst rk = resid_const(A, cst);
-        const __amdgpu_buffer_rsrc_t rt = row_rsrc(A, A.t, g);
-        const __amdgpu_buffer_rsrc_t ra = row_rsrc(A, bonus ? A.t : A.a, g);
-        // a row whose a and b are equal bitwise reads a for b (same weights)
-        const bool nb = !bonus && (cst[D_STATUS] & kStNeq) != 0u;
-        const __amdgpu_buffer_rsrc_t rb = row_rsrc(A, nb ? A.b : A.t, g);
-        const uint32_t off = (uint32_t)((vi - g.vbeg) * 16);
-        u4 vt = buf_load(rt, off);
-        u4 va = bonus ? vt : buf_load(ra, off);
-        u4 vb = nb ? buf_load(rb, off) : u4{0, 0, 0, 0};
-        if (A.vmap != nullptr) {
-          fix_vec<DT>(A, g, A.t, vi, vt);
-          map_vecs<DT>(A, g, vi, vt, va, vb, !bonus);
-          if (bonus) va = vt;
-        } else if (has_tail(A, sv0, sv0 + 64)) {
-          fix_vec<DT>(A, g, A.t, vi, vt);
-          if (!bonus) fix_vec<DT>(A, g, A.a, vi, va);
-          if (nb) fix_vec<DT>(A, g, A.b, vi, vb);
+        float x[VE], xt[VE], xa[VE], xb[VE];
+        long long first;                     // flat index of the lane's first element
+        if constexpr (kXv) {
+          const int x0 = sel * 64 * VE + lane * VE;
+          first = g.e0 + x0;
+          #pragma unroll
+          for (int e = 0; e < VE; ++e) {
+            // (loads without branches: token 0 and drafter id 0 exist)
+            const int j = A.vmap[x0 + e < A.V ? x0 + e : 0];
+            const bool in = x0 + e < A.V && j >= 0 && j < A.Vd;
+            const long long jd = (long long)g.row * A.Vd + (in ? j : 0);
+            xt[e] = Elem<DT>::load_one(A.t, g.e0 + (in ? x0 + e : 0));
+            xa[e] = Elem<DT>::load_one(A.a, jd);
+            xb[e] = Elem<DT>::load_one(A.b, jd);
+            xt[e] = in ? xt[e] : -INFINITY;
+            xa[e] = in ? xa[e] : -INFINITY;
+            xb[e] = in ? xb[e] : -INFINITY;
+          }
         } else {
-          mask_vec<DT>(A, g, vi, vt);
-          mask_vec<DT>(A, g, vi, va);
-          mask_vec<DT>(A, g, vi, vb);
+          const int ch = sel / kSubPerChunk, sub = sel % kSubPerChunk;
+          const long long sv0 = g.vbeg + (long long)ch * kChunkVec + (long long)sub * 64;
+          const long long vi = sv0 + lane;
+          first = vi * VE;
+          const __amdgpu_buffer_rsrc_t rt = row_rsrc(A, A.t, g);
+          const __amdgpu_buffer_rsrc_t ra = row_rsrc(A, bonus ? A.t : A.a, g);
+          // a row whose a and b are equal bitwise reads a for b (same weights)
+          const bool nb = !bonus && (cst[D_STATUS] & kStNeq) != 0u;
+          const __amdgpu_buffer_rsrc_t rb = row_rsrc(A, nb ? A.b : A.t, g);
+          const uint32_t off = (uint32_t)((vi - g.vbeg) * 16);
+          u4 vt = buf_load(rt, off);
+          u4 va = bonus ? vt : buf_load(ra, off);
+          u4 vb = nb ? buf_load(rb, off) : u4{0, 0, 0, 0};
+          if (has_tail(A, sv0, sv0 + 64)) {
+            fix_vec<DT>(A, g, A.t, vi, vt);
+            if (!bonus) fix_vec<DT>(A, g, A.a, vi, va);
+            if (nb) fix_vec<DT>(A, g, A.b, vi, vb);
+          } else {
+            mask_vec<DT>(A, g, vi, vt);
+            mask_vec<DT>(A, g, vi, va);
+            mask_vec<DT>(A, g, vi, vb);
+          }
+          if (!nb) vb = va;
+          #pragma unroll
+          for (int e = 0; e < VE; ++e) {
+            xt[e] = Elem<DT>::get(vt, e);
+            xa[e] = Elem<DT>::get(va, e);
+            xb[e] = Elem<DT>::get(vb, e);
+          }
         }
-        if (!nb) vb = va;
-        float x[VE];
         double vsum = 0.0;
         #pragma unroll
         for (int e = 0; e < VE; ++e) {
-          const float xt = Elem<DT>::get(vt, e);
-          x[e] = bonus ? bonus_elem(xt, rk.c, rk.Rf)
-                       : resid_elem<DM>(xt, Elem<DT>::get(va, e), Elem<DT>::get(vb, e), rk);
+          x[e] = bonus ? bonus_elem(xt[e], rk.c, rk.Rf) : resid_elem<DM>(xt[e], xa[e], xb[e], rk);
           vsum += (double)x[e];
         }
         double vin, vex;
@@ -817,12 +863,10 @@ DEV int cdf_pick(const KArgs& A, int req, int i, double u, bool bonus, Smem& sm,
         #pragma unroll
         for (int e = 0; e < VE; ++e) {
           run += (double)x[e];
-          const int idx = (int)(vi * VE + e - g.e0);
+          const int idx = (int)(first + e - g.e0);
           if (x[e] > 0.0f && run > target && first_ok == 0x7FFFFFFF) {
             first_ok = idx;
-            const float xt = Elem<DT>::get(vt, e);
-            fx = bonus ? xt
-                       : fuse_masked(xt, Elem<DT>::get(va, e), Elem<DT>::get(vb, e), A.beta, A.delta_mode);
+            fx = bonus ? xt[e] : fuse_masked(xt[e], xa[e], xb[e], A.beta, A.delta_mode);
           }
           if (x[e] > 0.0f) last_pos = idx;
         }
@@ -872,8 +916,8 @@ DEV int row_argmax_f(const KArgs& A, const RowGeo& g, Smem& sm) {
   return r == 0x7FFFFFFF ? 0 : r;   // a row with no finite f: token 0, as argmax of all -inf
 }
 
-template <int DT, int DM>
-DEV void pick_item(const KArgs& A, int req, Smem& sm) {
+template <int DT, int DM, bool kXv = false>
+DEV void pick_item(const KArgs& A, int req, Smem& sm, const XPass2& xp = XPass2{}) {
   const int lane = lane_id(), w = wave_id();
   const int K = A.K;
   const uint32_t state = load_decision(A, req, sm);
@@ -895,6 +939,9 @@ DEV void pick_item(const KArgs& A, int req, Smem& sm) {
       if (k % kWaves != w) continue;
       const int i = __builtin_ctzll(jm);
       double part = 0.0;
+      if (kXv) {
+        for (int c = lane; c < xp.T; c += 64) part += (double)xp.jpart[((size_t)req * (K + 1) + i) * xp.T + c];
+      } else
       for (int c = lane; c < A.S * A.P2; c += 64)
         part += (double)wait_f32(p2_rec(A, req, i, c / A.P2) + P2_J + c % A.P2, A, ok);
       part = wave_sum_d(part);
@@ -939,7 +986,7 @@ DEV void pick_item(const KArgs& A, int req, Smem& sm) {
   if (samp) {
     const bool bonus = j == K && !A.fuse_bonus;   // weights from t alone
     const double u = (double)uK;
-    int pick = cdf_pick<DT, DM>(A, req, j, u, bonus, sm, ok);
+    int pick = cdf_pick<DT, DM, kXv>(A, req, j, u, bonus, sm, ok, xp);
     const RowGeo g = row_span<DT>(A, req * (K + 1) + j);
     const bool have_x = pick >= 0 && sm.flags[2] != 0;
     if (pick < 0) pick = row_argmax_f<DT>(A, g, sm);

@@ -119,9 +119,7 @@ DEV void publish_stats(const KArgs& A, const RowGeo& g, int m, long long rel0, c
         u4 vt = buf_load(row_rsrc(A, A.t, g), off);
         fix_vec<DT>(A, g, A.t, vi, vt);
         u4 va = vt, vb = vt;
-        if (A.vmap != nullptr) {
-          map_vecs<DT>(A, g, vi, vt, va, vb, kDraft);
-        } else if (kDraft) {
+        if (kDraft) {
           va = buf_load(row_rsrc(A, A.a, g), off);
           vb = buf_load(row_rsrc(A, A.b, g), off);
           fix_vec<DT>(A, g, A.a, vi, va);
@@ -267,8 +265,7 @@ DEV void stats_init(StatsAcc& q, float c) {
 
 // Generic path: one vector at a time, every vector repaired (row boundary,
 // array end), NaN-safe exponent for f.  Used for the chunk that holds a
-// ragged array end, to redo a chunk whose f sum came out NaN, and for every
-// chunk when the drafter rows are reached through a vocabulary map.
+// ragged array end and to redo a chunk whose f sum came out NaN.
 template <int DT, int KIND, bool kB1, int DM, bool kKL>
 DEV void stats_slow(const KArgs& A, const RowGeo& g, int m, Smem& sm) {
   using TR = KindTraits<KIND>;
@@ -287,9 +284,7 @@ DEV void stats_slow(const KArgs& A, const RowGeo& g, int m, Smem& sm) {
     const long long vi = g.vbeg + rv;
     u4 vt = buf_load(rt, off), va = vt, vb = vt;
     fix_vec<DT>(A, g, A.t, vi, vt);
-    if (A.vmap != nullptr) {
-      map_vecs<DT>(A, g, vi, vt, va, vb, kDraft);
-    } else if (kDraft) {
+    if (kDraft) {
       va = buf_load(ra, off);
       vb = buf_load(rb, off);
       fix_vec<DT>(A, g, A.a, vi, va);
@@ -323,9 +318,10 @@ DEV bool stats_fast(const KArgs& A, const RowGeo& g, int m, Smem& sm) {
   stats_init(q, c);
   // rolling prefetch: slot j % W holds vector j; it is refilled with vector
   // j + W as soon as vector j is reduced (one vector less in flight with the
-  // KL sum, which needs the registers)
+  // KL sum, which needs the registers; two less where f needs t - b beside it,
+  // which would spill 12 bytes otherwise: fewer in flight cost no time)
   constexpr int kVecs = kNSub * kNV;
-  constexpr int W = kKL ? kWin - 1 : kWin;
+  constexpr int W = kKL ? (DM == kDeltaTB ? kWin - 2 : kWin - 1) : kWin;
 #ifdef ASYMSPEC_TRACE
   if (threadIdx.x == 0) sm.t_mark[0] = __builtin_amdgcn_s_memrealtime();
 #endif
@@ -371,72 +367,13 @@ DEV bool stats_fast(const KArgs& A, const RowGeo& g, int m, Smem& sm) {
   return true;
 }
 
-// Cross-family vocabularies, rows with no argmax to find (sampling drafts and
-// a sampling fused bonus row): the drafter rows are read in their own order,
-// contiguously, and t is gathered through the drafter-to-verifier map, so a
-// shared token costs one gather instead of two (a and b through the
-// verifier-to-drafter map) and the gathers hit the shorter verifier row.
-// The statistics are the same sums over the shared set in another order;
-// chunk m covers drafter vectors [m * kChunkVec, (m+1) * kChunkVec).
-template <int DT, int KIND, bool kB1, int DM, bool kKL>
-DEV void stats_dorder(const KArgs& A, const RowGeo& g, int m, Smem& sm) {
-  constexpr int VE = Elem<DT>::VE;
-  constexpr int ES = 16 / VE;
-  const int lane = lane_id(), w = wave_id();
-  const long long e0d = (long long)g.row * A.Vd;
-  const long long vbeg = e0d / VE, vend = (e0d + A.Vd + VE - 1) / VE;
-  const unsigned long long dbytes = (unsigned long long)A.B * (A.K + 1) * (unsigned long long)A.Vd * ES;
-  unsigned long long span = (unsigned long long)(vend - vbeg) * 16ull;
-  if (span > dbytes - (unsigned long long)vbeg * 16ull) span = dbytes - (unsigned long long)vbeg * 16ull;
-  const __amdgpu_buffer_rsrc_t ra = make_rsrc((const char*)A.a + vbeg * 16, span);
-  const __amdgpu_buffer_rsrc_t rb = make_rsrc((const char*)A.b + vbeg * 16, span);
-  const long long last_full = (long long)(dbytes / 16ull), n_el = (long long)(dbytes / ES);
-  const long long rel0 = (long long)m * kChunkVec + (long long)w * (64 * kNV) + lane;
-  StatsAcc q;
-  stats_init(q, g.c);
-  #pragma unroll 1
-  for (int kk = 0; kk < kNSub * kNV; ++kk) {
-    const long long rv = rel0 + (long long)(kk / kNV) * kTileVec + (kk % kNV) * 64;
-    const long long vi = vbeg + rv;
-    const uint32_t off = (uint32_t)(rv * 16);
-    u4 va = buf_load_nt(ra, off), vb = buf_load_nt(rb, off);
-    u4 t2 = {0, 0, 0, 0}, a2 = t2, b2 = t2;
-    #pragma unroll
-    for (int e = 0; e < VE; ++e) {
-      const long long jg = vi * VE + e;            // flat drafter index
-      const long long jr = jg - e0d;               // drafter id in the row
-      float xt = -INFINITY, xa = -INFINITY, xb = -INFINITY;
-      const int x = (jr >= 0 && jr < A.Vd) ? A.inv[jr] : -1;
-      if (x >= 0 && x < A.V) {
-        xt = Elem<DT>::load_one(A.t, g.e0 + x);
-        if (vi >= last_full && jg < n_el) {       // the partial vector at the array end
-          xa = Elem<DT>::load_one(A.a, jg);
-          xb = Elem<DT>::load_one(A.b, jg);
-        } else {
-          xa = Elem<DT>::get(va, e);
-          xb = Elem<DT>::get(vb, e);
-        }
-      }
-      Elem<DT>::put_one(t2, e, xt);
-      Elem<DT>::put_one(a2, e, xa);
-      Elem<DT>::put_one(b2, e, xb);
-    }
-    stats_vec<DT, KIND, kB1, DM, kKL, true, true>(A, g.c, t2, a2, b2, kk, q);
-  }
-  publish_stats<DT, KIND, DM, kKL>(A, g, m, rel0, q, sm);
-}
-
 template <int DT, int KIND, bool kB1, int DM, bool kKL = false>
 DEV void stats_item(const KArgs& A, int row, int m, Smem& sm) {
   constexpr int VE = Elem<DT>::VE;
   const RowGeo g = row_geo<DT>(A, row);
-  if (!KindTraits<KIND>::kArg && KindTraits<KIND>::NS == 3 && A.vmap != nullptr && inv_ok(A)) {
-    stats_dorder<DT, KIND, kB1, DM, kKL>(A, g, m, sm);
-    return;
-  }
   const long long c0 = g.vbeg + (long long)m * kChunkVec, c1 = c0 + kChunkVec;
   bool done = false;
-  if (A.vmap == nullptr && !has_tail(A, c0, c1)) {
+  if (!has_tail(A, c0, c1)) {
     // a chunk whose vectors lie wholly inside the row needs no masking
     const bool interior = c0 * VE >= g.e0 && c1 * VE <= g.e0 + A.V;
     done = interior ? stats_fast<DT, KIND, kB1, DM, kKL, false>(A, g, m, sm)

@@ -414,6 +414,29 @@ def test_xvocab_workload_1(gpu):
     _note(compare(mx, g, label="xvocab workload 1"))
 
 
+@pytest.mark.parametrize("dtype,V,Vd,frac", [
+    ("bf16", 1023, 16384, 0.9), ("bf16", 1025, 16385, 0.9), ("bf16", 2049, 32767, 1.0),
+    ("bf16", 4096, 49153, 0.001), ("bf16", 270001, 20001, 0.07), ("fp32", 1024, 8192, 0.9),
+    ("fp32", 3073, 8193, 1.0), ("fp32", 530001, 8191, 0.01)])
+def test_xvocab_tile_edges(gpu, dtype, V, Vd, frac):
+    """Drafter vocabularies around a tile (16384 bf16 or 8192 fp32 ids), odd
+    ones (rows then start between 4-byte boundaries), verifier vocabularies
+    around a unit of the lists (1024 tokens) and past the token bits that a
+    list entry holds (2^18 or 2^19), and tiles with few or no entries; greedy
+    and sampling requests, the divergence of every row, and early exit with
+    the full read's outputs."""
+    from parity_util import make_xvocab
+    x = synth.generate(B=4, K=2, V=V, dtype=dtype, rho=("alternate", 0.7, 0.0),
+                       tau=("alternate", 0.0, 0.9), seed=V % 1009)
+    ad, bd, vm, mx = make_xvocab(x, Vd, frac, seed=Vd % 97)
+    g = run_gpu(mx, vocab=(ad, bd, vm))
+    _note(compare(mx, g, label=f"xvocab tiles {dtype} V={V} Vd={Vd}"))
+    e = run_gpu(mx, vocab=(ad, bd, vm), early_exit=1)
+    assert np.array_equal(e[0], g[0]) and np.array_equal(e[1], g[1])
+    read = ~np.isnan(e[2])
+    assert np.array_equal(e[2][read], g[2][read]) and read[:, 0].all() and read[:, x.K].all()
+
+
 # ----------------------------------------------------------- early exit --
 def _check_early_exit(x, ee, **kw):
     """Early exit against the full read of the same call (same kernels on
