@@ -165,11 +165,13 @@ int asymspec_workspace_clear(void* workspace, size_t workspace_bytes, void* stre
  *                       element's log-probability under its row's distribution:
  *                       rows i < K log softmax(f_i/tau), row K log softmax(t_K/tau)
  *                       (of f_K with ASYMSPEC_FUSE_BONUS), tau = 1 for greedy
- *                       requests; -inf where f is not a number.  Written by a
- *                       second kernel on `stream` that reads the logits again
- *                       (3 (K+1) V elements) and writes 4 (K+1) V bytes per request;
- *                       one workgroup per 32 KiB chunk of a row, so B (K+1) times
- *                       the chunks per row must stay below 2^31 (else E_ARG)
+ *                       requests; -inf where f is not a number.  Written by
+ *                       the workgroups that read the logits, from registers
+ *                       (4 (K+1) V bytes per request), or, with the KL gate and
+ *                       for cross-family calls, by a second kernel on `stream`
+ *                       that reads them again; one workgroup per 32 KiB chunk
+ *                       of a row, so B (K+1) times the chunks per row must stay
+ *                       below 2^31 (else E_ARG)
  *   workspace           device scratch of >= asymspec_workspace_size bytes,
  *                       256-byte aligned, contents opaque between calls
  *   stream              hipStream_t or NULL

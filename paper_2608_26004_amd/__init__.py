@@ -174,7 +174,7 @@ def fuse_verify(t, a, b, draft_tokens, draft_probs, uniforms, temperature,
     scale lam); delta_mode: DELTA_AB (the paper), DELTA_A or DELTA_TB;
     fuse_bonus: take the bonus token from f_K rather than t_K (FUSE_BONUS);
     return_full: also return every element's log-probability under its row's
-    distribution, [B, K+1, V] float32 (a second pass over the logits);
+    distribution, [B, K+1, V] float32;
     vocab_map: for a drafter of another model family, [V] int32 on the GPU
     (drafter id of each verifier token, -1 if not shared); a and b are then
     [B, K+1, Vd] in the drafter's vocabulary;

@@ -34,7 +34,7 @@ def units():
     for dt in (0, 1):
         out.append((f"xv_{dt}", "xvocab.hip", [f"-DASYMSPEC_PART_DT={dt}"]))
         for dm in (0, 1, 2):
-            for var in (0, 1, 2):
+            for var in (0, 1, 2, 3):
                 out.append((f"fv_{dt}{dm}{var}", "kernels.hip",
                             [f"-DASYMSPEC_PART_DT={dt}", f"-DASYMSPEC_PART_DM={dm}", f"-DASYMSPEC_PART_VAR={var}"]))
     return out

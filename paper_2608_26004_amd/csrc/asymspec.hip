@@ -109,6 +109,7 @@ struct DevInfo {
   int ok = 0;
   int n_cu = 0;
   int max_blocks[2] = {0, 0};   // co-resident workgroups, per dtype
+  int max_blocks_full[2] = {0, 0};   // the same for the full-row instances
 };
 
 static DevInfo g_dev[64];
@@ -118,22 +119,23 @@ static_assert(kDeltaAB == ASYMSPEC_DELTA_AB && kDeltaA == ASYMSPEC_DELTA_A && kD
               "delta sources");
 
 // One kernel per storage type, source of delta and variant (kernels.hip):
-// beta == 1, any beta, and the KL gate (beta taken at run time: fl(1 * x) = x,
-// so a call with beta = 1 computes the same values).
+// beta == 1, any beta, the KL gate, and the full rows (the last two take beta at
+// run time: fl(1 * x) = x, so a call with beta = 1 computes the same values).
 template <int DT, int DM>
-static const void* kernel_ptr_dm(bool beta1, bool kl) {
-  return kl ? fuse_verify_ptr<DT, DM, kVarKL>()
-            : (beta1 ? fuse_verify_ptr<DT, DM, kVarBeta1>() : fuse_verify_ptr<DT, DM, kVarBeta>());
+static const void* kernel_ptr_dm(int var) {
+  return var == kVarBeta1  ? fuse_verify_ptr<DT, DM, kVarBeta1>()
+         : var == kVarBeta ? fuse_verify_ptr<DT, DM, kVarBeta>()
+         : var == kVarKL   ? fuse_verify_ptr<DT, DM, kVarKL>()
+                           : fuse_verify_ptr<DT, DM, kVarFull>();
 }
 template <int DT>
-static const void* kernel_ptr_dt(bool beta1, int dm, bool kl) {
-  if (dm == kDeltaA) return kernel_ptr_dm<DT, kDeltaA>(beta1, kl);
-  if (dm == kDeltaTB) return kernel_ptr_dm<DT, kDeltaTB>(beta1, kl);
-  return kernel_ptr_dm<DT, kDeltaAB>(beta1, kl);
+static const void* kernel_ptr_dt(int var, int dm) {
+  if (dm == kDeltaA) return kernel_ptr_dm<DT, kDeltaA>(var);
+  if (dm == kDeltaTB) return kernel_ptr_dm<DT, kDeltaTB>(var);
+  return kernel_ptr_dm<DT, kDeltaAB>(var);
 }
-static const void* kernel_ptr(int dtype, bool beta1, int dm, bool kl) {
-  return dtype == ASYMSPEC_BF16 ? kernel_ptr_dt<ASYMSPEC_BF16>(beta1, dm, kl)
-                                : kernel_ptr_dt<ASYMSPEC_FP32>(beta1, dm, kl);
+static const void* kernel_ptr(int dtype, int var, int dm) {
+  return dtype == ASYMSPEC_BF16 ? kernel_ptr_dt<ASYMSPEC_BF16>(var, dm) : kernel_ptr_dt<ASYMSPEC_FP32>(var, dm);
 }
 template <int DT>
 static const void* dump_ptr_dt(int dm) {
@@ -156,16 +158,17 @@ static const DevInfo* device_info() {
   if (std::strncmp(pr.gcnArchName, "gfx950", 6) != 0) return nullptr;
   di.n_cu = pr.multiProcessorCount;
   for (int dt = 0; dt < 2; ++dt) {
-    int nb = 1 << 30;
-    for (int v = 0; v < 3; ++v)
+    int nb = 1 << 30, nf = 1 << 30;
+    for (int v = kVarBeta1; v <= kVarFull; ++v)
       for (int dm = 0; dm < 3; ++dm) {
         int x = 0;
-        const void* k = kernel_ptr(dt, v == 0, dm, v == 2);
+        const void* k = kernel_ptr(dt, v, dm);
         if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&x, k, kThreads, 0) != hipSuccess) return nullptr;
-        nb = std::min(nb, x);
+        (v == kVarFull ? nf : nb) = std::min(v == kVarFull ? nf : nb, x);
       }
-    if (nb < 1) return nullptr;
+    if (nb < 1 || nf < 1) return nullptr;
     di.max_blocks[dt] = nb * di.n_cu;
+    di.max_blocks_full[dt] = nf * di.n_cu;
   }
   di.ok = 1;
   return &di;
@@ -320,7 +323,13 @@ static int fuse_verify_impl(const void* t, const void* a, const void* b, int dty
   A.poll_ticks = g_poll_ticks.load();
   // lags scale with the number of workgroups the chip holds at once
   const int ee_rows = ee ? (params->early_rows > 0 ? params->early_rows : 2) : 0;
-  const int in_flight = di->max_blocks[dtype];
+  // the full rows are written by the statistics items, or by a second kernel
+  // (a row's items wait for each other: its share of an XCD must fit there)
+  const bool kl = params->gate_mode == ASYMSPEC_GATE_KL;
+  const bool in_stats = fused_logprobs_full != nullptr && vmap == nullptr && !kl &&
+                        (L.S + 7) / 8 + 1 <= di->max_blocks_full[dtype] / 8;
+  A.full = in_stats ? fused_logprobs_full : nullptr;
+  const int in_flight = in_stats ? di->max_blocks_full[dtype] : di->max_blocks[dtype];
   // pass 2 in 8, 4 or 2 items per chunk while that many still fit on the
   // chip at once: a small batch leaves most of it idle, and pass 2's
   // divergence terms are arithmetic-bound within one workgroup
@@ -350,11 +359,15 @@ static int fuse_verify_impl(const void* t, const void* a, const void* b, int dty
             : xv_launch<ASYMSPEC_FP32>(A, L.xv, ws + L.off_xv, ee_rows, di->n_cu, (hipStream_t)stream);
   } else {
     void* args[] = {&A};
-    e = hipLaunchKernel(kernel_ptr(dtype, params->beta == 1.0f, params->delta_mode,
-                                   params->gate_mode == ASYMSPEC_GATE_KL), dim3(grid),
-                                   dim3(kThreads), args, 0, (hipStream_t)stream);
+    const int var = in_stats ? kVarFull : kl ? kVarKL : params->beta == 1.0f ? kVarBeta1 : kVarBeta;
+    e = hipLaunchKernel(kernel_ptr(dtype, var, params->delta_mode), dim3(grid), dim3(kThreads), args, 0,
+                        (hipStream_t)stream);
+    if (e == hipSuccess && in_stats) {
+      hipLaunchKernelGGL(full_check_kernel, dim3((B + 255) / 256), dim3(256), 0, (hipStream_t)stream, A);
+      e = hipGetLastError();
+    }
   }
-  if (e == hipSuccess && fused_logprobs_full != nullptr) {
+  if (e == hipSuccess && fused_logprobs_full != nullptr && !in_stats) {
     // one workgroup per (row, chunk), after the decision kernel on the stream
     float* full = fused_logprobs_full;
     void* dargs[] = {&A, &full};

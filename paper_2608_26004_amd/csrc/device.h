@@ -79,7 +79,8 @@ enum { R1_R = 0, R1_S = kSlots, R1_ARG = 2 * kSlots, R1_NEQ = 2 * kSlots + 1, R1
 // Decision record of one request: a header and one block per row, published
 // by the decide item; pass-2 and pick items load it into LDS (Smem::req,
 // Smem::rows).
-enum { H_STATE = 0, H_J = 1, H_TASK_LO = 2, H_TASK_HI = 3, H_SAMP = 4, H_USED = 5, H_VERDICT = 5, kDecHdr = 8 };
+enum { H_STATE = 0, H_J = 1, H_TASK_LO = 2, H_TASK_HI = 3, H_SAMP = 4, H_USED = 5, H_VERDICT = 5, H_FULL = 6, kDecHdr = 8 };
+// H_FULL: set when the request's full rows could not be completed.
 // Early exit: the verdict on a request's first rows (a sure rejection among
 // them makes the other rows unneeded).
 enum { kVerdictRead = 1, kVerdictSkip = 2 };
@@ -122,6 +123,7 @@ struct KArgs {
   const void* t; const void* a; const void* b;
   const int32_t* d; const float* dp; const float* u; const float* tau;
   int32_t* acc_out; int32_t* next_out; float* flp_out; float* gate_out;
+  float* full;        // full log-probability rows written by the statistics items
   uint64_t* rec1; uint64_t* dec; uint64_t* rec2;
   uint32_t* err;
   unsigned long long stream_bytes;   // bytes of each logit array
@@ -146,6 +148,14 @@ struct KArgs {
   unsigned trace_items;   // items the timeline holds
 #endif
 };
+
+// Decision header of a request, and decision block of its row i.
+DEV uint64_t* dec_hdr(const KArgs& A, int req) {
+  return A.dec + (size_t)req * (kDecHdr + (size_t)(A.K + 1) * kDecRow);
+}
+DEV uint64_t* dec_row(const KArgs& A, int req, int i) {
+  return dec_hdr(A, req) + kDecHdr + (size_t)i * kDecRow;
+}
 
 // Thread coordinates for item code.  They pass through empty asm so that the
 // compiler cannot hoist index arithmetic of one item type out of the

@@ -10,36 +10,39 @@
 
 namespace asym {
 
-template <int DT, bool kB1, int DM, bool kKL>
+template <int DT, bool kB1, int DM, bool kKL, bool kFull>
 DEV void stats_chunk(const KArgs& A, int req, int i, int m, Smem& sm) {
   const int row = req * (A.K + 1) + i;
   const float tau = sload_f32(A.tau, req);
   if (i == A.K) {
     if (A.fuse_bonus) {
-      if (tau > 0.0f) stats_item<DT, kSampleBonusF, kB1, DM>(A, row, m, sm);
-      else stats_item<DT, kGreedyBonusF, kB1, DM>(A, row, m, sm);
+      if (tau > 0.0f) stats_item<DT, kSampleBonusF, kB1, DM, false, kFull>(A, row, m, sm);
+      else stats_item<DT, kGreedyBonusF, kB1, DM, false, kFull>(A, row, m, sm);
     } else if (tau > 0.0f) {
-      stats_item<DT, kSampleBonus, kB1, DM>(A, row, m, sm);
+      stats_item<DT, kSampleBonus, kB1, DM, false, kFull>(A, row, m, sm);
     } else {
-      stats_item<DT, kGreedyBonus, kB1, DM>(A, row, m, sm);
+      stats_item<DT, kGreedyBonus, kB1, DM, false, kFull>(A, row, m, sm);
     }
   } else if (!(tau > 0.0f)) {
-    stats_item<DT, kGreedyDraft, kB1, DM, kKL>(A, row, m, sm);
+    stats_item<DT, kGreedyDraft, kB1, DM, kKL, kFull>(A, row, m, sm);
   } else if (tau == 1.0f) {
-    stats_item<DT, kSampleDraft1, kB1, DM, kKL>(A, row, m, sm);
+    stats_item<DT, kSampleDraft1, kB1, DM, kKL, kFull>(A, row, m, sm);
   } else {
-    stats_item<DT, kSampleDraftT, kB1, DM, kKL>(A, row, m, sm);
+    stats_item<DT, kSampleDraftT, kB1, DM, kKL, kFull>(A, row, m, sm);
   }
 }
 
-template <int DT, bool kB1, int DM, bool kKL>
+template <int DT, bool kB1, int DM, bool kKL, bool kFull>
 DEV void stats_dispatch(const KArgs& A, int req, int sub, Smem& sm) {
   const int i = sub / A.S, m = sub - i * A.S;
-  stats_chunk<DT, kB1, DM, kKL>(A, req, i, m, sm);
+  stats_chunk<DT, kB1, DM, kKL, kFull>(A, req, i, m, sm);
 }
 
 #ifndef ASYMSPEC_WAVES
 #define ASYMSPEC_WAVES 4
+#endif
+#ifndef ASYMSPEC_WAVES_FULL
+#define ASYMSPEC_WAVES_FULL 3
 #endif
 
 // One workgroup per item.  An item waits only for items earlier in the list
@@ -51,8 +54,11 @@ DEV void stats_dispatch(const KArgs& A, int req, int sub, Smem& sm) {
 // kKL: calls with the KL gate, whose draft rows also sum the divergence
 // beside the A slot (a kernel of its own, so that the extra registers of
 // those items do not weigh on the other gates' kernels).
-template <int DT, bool kB1, int DM, bool kKL>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(ASYMSPEC_WAVES)))
+// kFull: calls with the full log-probability rows, whose statistics items keep
+// their chunk's emission logits (64 registers a thread in bf16, so three
+// workgroups per CU) and write them once the row's records are in.
+template <int DT, bool kB1, int DM, bool kKL, bool kFull>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kFull ? ASYMSPEC_WAVES_FULL : ASYMSPEC_WAVES)))
 void fuse_verify_kernel(KArgs A) {
   __shared__ Smem sm;
 #ifdef ASYMSPEC_TRACE
@@ -68,7 +74,7 @@ void fuse_verify_kernel(KArgs A) {
   }
   // one call site per item kind keeps a single inlined copy of each
   switch (type) {
-    case kItemStats: stats_dispatch<DT, kB1, DM, kKL>(A, it.req, it.sub, sm); break;
+    case kItemStats: stats_dispatch<DT, kB1, DM, kKL, kFull>(A, it.req, it.sub, sm); break;
     case kItemVerdict:
     case kItemDecide: decide_item<DT>(A, it.req, sm, type == kItemVerdict); break;
     case kItemPass2: pass2_item<DT, DM>(A, it.req, it.sub, sm); break;

@@ -7,7 +7,7 @@
 
 namespace asym {
 
-enum { kVarBeta1 = 0, kVarBeta = 1, kVarKL = 2 };
+enum { kVarBeta1 = 0, kVarBeta = 1, kVarKL = 2, kVarFull = 3 };
 
 template <int DT, int DM, int VAR>
 const void* fuse_verify_ptr();

@@ -12,7 +12,8 @@ namespace asym {
 template <>
 const void* fuse_verify_ptr<ASYMSPEC_PART_DT, ASYMSPEC_PART_DM, ASYMSPEC_PART_VAR>() {
   constexpr bool kB1 = ASYMSPEC_PART_VAR == kVarBeta1, kKL = ASYMSPEC_PART_VAR == kVarKL;
-  return (const void*)fuse_verify_kernel<ASYMSPEC_PART_DT, kB1, ASYMSPEC_PART_DM, kKL>;
+  constexpr bool kFull = ASYMSPEC_PART_VAR == kVarFull;
+  return (const void*)fuse_verify_kernel<ASYMSPEC_PART_DT, kB1, ASYMSPEC_PART_DM, kKL, kFull>;
 }
 
 }  // namespace asym

@@ -24,12 +24,6 @@
 
 namespace asym {
 
-DEV uint64_t* dec_hdr(const KArgs& A, int req) {
-  return A.dec + (size_t)req * (kDecHdr + (size_t)(A.K + 1) * kDecRow);
-}
-DEV uint64_t* dec_row(const KArgs& A, int req, int i) {
-  return dec_hdr(A, req) + kDecHdr + (size_t)i * kDecRow;
-}
 DEV uint64_t* p2_rec(const KArgs& A, int req, int i, int m) {
   return A.rec2 + (((size_t)req * (A.K + 1) + i) * A.S + m) * kR2;
 }

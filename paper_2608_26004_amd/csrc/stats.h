@@ -18,6 +18,7 @@
 #define ASYMSPEC_STATS_H_
 
 #include "device.h"
+#include "full.h"
 
 namespace asym {
 
@@ -196,9 +197,11 @@ DEV void acc_sum(Acc& q, const float (&x)[VE], float c) {
   else acc_vec_lazy<VE, kClamp>(q, x, c);
 }
 
-// One vector of each stream into the accumulators.
+// One vector of each stream into the accumulators.  keep (full rows): where the
+// emission logits (f, or t for the plain bonus row) stay, else null.
 template <int DT, int KIND, bool kB1, int DM, bool kKL, bool kClamp, bool kFirst>
-DEV void stats_vec(const KArgs& A, float c, const u4& vt, const u4& va, const u4& vb, int kk, StatsAcc& q) {
+DEV void stats_vec(const KArgs& A, float c, const u4& vt, const u4& va, const u4& vb, int kk, StatsAcc& q,
+                   float* keep = nullptr) {
   using TR = KindTraits<KIND>;
   constexpr int VE = Elem<DT>::VE;
   float xt[VE];
@@ -211,6 +214,7 @@ DEV void stats_vec(const KArgs& A, float c, const u4& vt, const u4& va, const u4
       xa[e] = Elem<DT>::get(va, e);
       xb[e] = Elem<DT>::get(vb, e);
       xf[e] = kB1 ? fuse1<DM>(xt[e], xa[e], xb[e]) : fuse<DM>(xt[e], xa[e], xb[e], A.beta);
+      if (keep != nullptr) keep[e] = xf[e];
     }
     // the compare is folded into a wave mask at once and pinned there: left
     // to itself the compiler re-materialises it at its only use, keeping
@@ -246,6 +250,9 @@ DEV void stats_vec(const KArgs& A, float c, const u4& vt, const u4& va, const u4
     if (TR::kB) pin_lazy(q.B);
     if (TR::kAT) pin_lazy(q.AT);
   } else {
+    #pragma unroll
+    for (int e = 0; e < VE; ++e)
+      if (keep != nullptr) keep[e] = xt[e];
     if (TR::kArg) {
       acc_vec<VE, false, true>(q.T, xt, c, kk);
       pin(q.T);
@@ -298,7 +305,7 @@ DEV void stats_slow(const KArgs& A, const RowGeo& g, int m, Smem& sm) {
 // Fast path; kMask for the first and last chunk of a row (elements outside
 // the row are masked, without branches).  Returns false, without publishing,
 // when the chunk must be redone on the generic path.
-template <int DT, int KIND, bool kB1, int DM, bool kKL, bool kMask>
+template <int DT, int KIND, bool kB1, int DM, bool kKL, bool kMask, bool kFull>
 DEV bool stats_fast(const KArgs& A, const RowGeo& g, int m, Smem& sm) {
   using TR = KindTraits<KIND>;
   constexpr int VE = Elem<DT>::VE;
@@ -326,6 +333,7 @@ DEV bool stats_fast(const KArgs& A, const RowGeo& g, int m, Smem& sm) {
   if (threadIdx.x == 0) sm.t_mark[0] = __builtin_amdgcn_s_memrealtime();
 #endif
   u4 buf[3][W];
+  float keep[kFull ? kVecs : 1][VE];
   #pragma unroll
   for (int j = 0; j < W; ++j)
     #pragma unroll
@@ -344,10 +352,11 @@ DEV bool stats_fast(const KArgs& A, const RowGeo& g, int m, Smem& sm) {
     // chunks clamp the exponent of f
     if (j == 0)
       stats_vec<DT, KIND, kB1, DM, kKL, kMask, true>(A, c, buf[0][sl], buf[NS == 3 ? 1 : 0][sl],
-                                                     buf[NS == 3 ? 2 : 0][sl], j, q);
+                                                     buf[NS == 3 ? 2 : 0][sl], j, q, kFull ? keep[0] : nullptr);
     else
       stats_vec<DT, KIND, kB1, DM, kKL, kMask, false>(A, c, buf[0][sl], buf[NS == 3 ? 1 : 0][sl],
-                                                      buf[NS == 3 ? 2 : 0][sl], j, q);
+                                                      buf[NS == 3 ? 2 : 0][sl], j, q,
+                                                      kFull ? keep[kFull ? j : 0] : nullptr);
     if (j + W < kVecs) {
       #pragma unroll
       for (int s = 0; s < NS; ++s) buf[s][sl] = buf_load_nt(r[s], off0 + (uint32_t)(vec_rel(j + W) * 16));
@@ -364,10 +373,17 @@ DEV bool stats_fast(const KArgs& A, const RowGeo& g, int m, Smem& sm) {
 #endif
   if (kDraft && !kMask && __syncthreads_or(q.F.s != q.F.s)) return false;
   publish_stats<DT, KIND, DM, kKL>(A, g, m, rel0, q, sm);
+  if (kFull) {
+    double l2;
+    if (full_norm<TR::argslot>(A, g, sm, l2)) {
+      #pragma unroll
+      for (int j = 0; j < kVecs; ++j) full_store<DT>(A, g, rel0 + vec_rel(j), keep[kFull ? j : 0], (double)c, l2);
+    }
+  }
   return true;
 }
 
-template <int DT, int KIND, bool kB1, int DM, bool kKL = false>
+template <int DT, int KIND, bool kB1, int DM, bool kKL, bool kFull>
 DEV void stats_item(const KArgs& A, int row, int m, Smem& sm) {
   constexpr int VE = Elem<DT>::VE;
   const RowGeo g = row_geo<DT>(A, row);
@@ -376,10 +392,19 @@ DEV void stats_item(const KArgs& A, int row, int m, Smem& sm) {
   if (!has_tail(A, c0, c1)) {
     // a chunk whose vectors lie wholly inside the row needs no masking
     const bool interior = c0 * VE >= g.e0 && c1 * VE <= g.e0 + A.V;
-    done = interior ? stats_fast<DT, KIND, kB1, DM, kKL, false>(A, g, m, sm)
-                    : stats_fast<DT, KIND, kB1, DM, kKL, true>(A, g, m, sm);
+    done = interior ? stats_fast<DT, KIND, kB1, DM, kKL, false, kFull>(A, g, m, sm)
+                    : stats_fast<DT, KIND, kB1, DM, kKL, true, kFull>(A, g, m, sm);
   }
-  if (!done) stats_slow<DT, KIND, kB1, DM, kKL>(A, g, m, sm);
+  if (!done) {
+    stats_slow<DT, KIND, kB1, DM, kKL>(A, g, m, sm);
+    if (kFull) {
+      // nothing was kept on this path: the chunk is read again
+      constexpr bool kFused = KindTraits<KIND>::NS == 3;
+      double l2;
+      if (full_norm<KindTraits<KIND>::argslot>(A, g, sm, l2))
+        full_chunk<DT, DM>(A, A.full, g, m, kFused, kFused, (double)g.c, l2);
+    }
+  }
 }
 
 }  // namespace asym

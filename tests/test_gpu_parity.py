@@ -361,6 +361,48 @@ def test_full_logprobs_workload_1(gpu):
     print(f"[full] workload 1: max abs err {err:.2e}")
 
 
+@pytest.mark.parametrize("dtype,V,K", [
+    ("bf16", 16383, 1), ("bf16", 16384, 2), ("bf16", 16385, 1), ("bf16", 40001, 2), ("fp32", 8192, 1),
+    ("fp32", 24577, 2), ("bf16", 270001, 1), ("fp32", 530003, 1)])
+def test_full_logprobs_chunks(gpu, dtype, V, K):
+    """The items of a row wait for each other's records before they write:
+    rows of 1, 2, 3, 17 and 65 chunks and around their edges, rows that start
+    mid-vector, and tokens that both drafter views mask inside a whole chunk
+    (its sum is redone on the generic path and the chunk read again)."""
+    x = synth.generate(B=3, K=K, V=V, dtype=dtype, rho=("alternate", 0.0, 2.0),
+                       tau=("alternate", 0.8, 0.0), seed=V % 997)
+    neg = np.float32(-np.inf) if dtype == "fp32" else np.uint16(0xFF80)
+    x.a[1, :, 100:103] = neg
+    x.b[1, :, 100:103] = neg
+    for fb in (False, True):
+        g = run_gpu(x, fuse_bonus=fb, want_full=True)
+        _note(compare(x, g, fuse_bonus=fb, label=f"full chunks {dtype} V={V} fb={fb}"))
+        compare_full(x, g[4], fuse_bonus=fb, label=f"full chunks {dtype} V={V} fb={fb}")
+
+
+def test_full_logprobs_timed_out_rows_are_marked(gpu):
+    """A wait bound of 20 ns: a request whose rows could not all be written
+    has accept_len = -1; the full rows of the others are the oracle's."""
+    import paper_2608_26004_amd as asp
+    import torch
+    from parity_util import to_device
+    x = synth.generate(B=40, K=2, V=50000, dtype="bf16", rho=("uniform", 0.0, 2.0),
+                       tau=("alternate", 0.0, 1.0), seed=77)
+    args = [to_device(v) for v in (x.t, x.a, x.b, x.draft_tokens, x.draft_probs, x.uniforms, x.temperature)]
+    ws = asp.Workspace(torch.device("cuda"))
+    try:
+        asp.set_wait_limit(2)
+        acc, _, _, full = asp.fuse_verify(*args, return_full=True, workspace=ws)
+        torch.cuda.synchronize()
+    finally:
+        asp.set_wait_limit(0)
+    good = np.nonzero(acc.cpu().numpy() >= 0)[0]
+    print(f"[timeouts] full rows: {ws.timeouts()} timed-out waits, {x.B - len(good)} of {x.B} requests marked")
+    assert ws.timeouts() > 0 and len(good) < x.B
+    if len(good):
+        compare_full(x, full.cpu().numpy(), requests=good.tolist(), label="full rows beside timed-out ones")
+
+
 # ------------------------------------------- cross-family vocabularies --
 # Sec. 6.4 / App. D: the drafter in its own vocabulary, reached through the
 # map; the oracle sees the rows carried into the verifier's vocabulary.
