@@ -338,7 +338,8 @@ static int fuse_verify_impl(const void* t, const void* a, const void* b, int dty
   while (A.P2 < kMaxP2 && p2_items * 2 * A.P2 <= in_flight) A.P2 *= 2;
   // with the gate output and a JSD-based gate, pass 2 sums the divergence of
   // every draft row whose views differ, not only of the open ones: at least
-  // two parts per chunk then shorten the last requests' pass 2
+  // two parts per chunk then shorten the last requests' pass 2 (B = 128, K = 6,
+  // V = 151936: 210 us with one, 195 with two; four were 4 us slower than two)
   if (A.want_gate && params->gate_mode != ASYMSPEC_GATE_KL && params->gate_mode != ASYMSPEC_GATE_LAMBDA &&
       A.P2 < 2)
     A.P2 = 2;

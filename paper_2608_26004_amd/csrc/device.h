@@ -95,8 +95,7 @@ enum {
   D_RF,         // reference exponent of p~ (drafts) or of the bonus weights
   D_ISF,        // 1 / sum of p~ weights (drafts)
   D_RQ, D_ISQ,  // the same for the proposal q = softmax(a / tau)
-  D_RA, D_RB,   // reference exponents of a and b at temperature 1 (JSD)
-  D_KAHI, D_KALO, D_KBHI, D_KBLO,  // log2 of the a and b sums, as hi + lo floats
+  D_JLA, D_JLB, D_JSA, D_JSB,   // JSD terms (JsdConst)
   D_LPD,        // log p~(d): fused log-probability of the draft token
   D_STATUS,     // kStDecided | kStAccept | kStDraft | kStNeq
   D_THR_LO, D_THR_HI,   // open rows: accepted iff D > thr (fp64)
@@ -665,17 +664,40 @@ DEV float resid_elem(float t, float a, float b, const ResidConst& k) {
 DEV float bonus_elem(float t, float c, float Rt) {
   return __builtin_amdgcn_exp2f(__builtin_fmaf(t, c, -Rt));
 }
-// JSD term P log2(2P/(P+Q)) + Q log2(2Q/(P+Q)) with P = softmax(a), Q =
-// softmax(b) (Eq. 3), from log2 P and log2 Q.
-struct JsdConst { float Ra, Rb, kahi, kalo, kbhi, kblo; };
-DEV float jsd_elem(float a, float b, const JsdConst& k) {
-  const float lp = (fmaxf(__builtin_fmaf(a, kL2E, -k.Ra), kFloorM) - k.kahi) - k.kalo;
-  const float lq = (fmaxf(__builtin_fmaf(b, kL2E, -k.Rb), kFloorM) - k.kbhi) - k.kblo;
-  const float P = __builtin_amdgcn_exp2f(lp);
-  const float Q = __builtin_amdgcn_exp2f(lq);
-  const float g = 1.0f - __builtin_amdgcn_logf(fmaxf(P + Q, 1e-37f));
-  return __builtin_fmaf(P, lp + g, Q * (lq + g));
+// JSD term P log2(2P/(P+Q)) + Q log2(2Q/(P+Q)), P = softmax(a), Q = softmax(b)
+// (Eq. 3), its two halves summed apart.  log2 P = a log2 e - LA uses La =
+// fl(LA): the rounding LA - La changes the logarithms of P and P + Q such that it
+// cancels from the sum of the terms to first order, and scales P, which sa
+// takes back from the half's sum (sb likewise).  10 plain and 3 transcendental
+// operations a pair; with LA in two words they were 16 and 3 (B = 128, K = 6, V =
+// 151936 with the gate output, bound by these operations: 206 -> 196 us; error
+// of D and the threshold against 64 bits 3.3e-7 either way).  log2 of (P + Q) / 2
+// in place of 1 - log2(P + Q) was 3.7e-7.  Logarithms are raised to -100 (a
+// token a view masks would give 0 * inf); such a P counts for nothing.
+struct JsdConst { float La, Lb, sa, sb; };
+DEV JsdConst jsd_make(double LA, double LB) {
+  const float La = (float)LA, Lb = (float)LB;
+  return JsdConst{La, Lb, (float)(1.0 + ((double)La - LA) * kLn2), (float)(1.0 + ((double)Lb - LB) * kLn2)};
 }
+struct JsdAcc { float p, q; };
+DEV void jsd_add(JsdAcc& acc, float a, float b, const JsdConst& k) {
+  const float lp = fmaxf(__builtin_fmaf(a, kL2E, -k.La), -100.0f);
+  const float lq = fmaxf(__builtin_fmaf(b, kL2E, -k.Lb), -100.0f);
+  const float P = __builtin_amdgcn_exp2f(lp), Q = __builtin_amdgcn_exp2f(lq);
+  const float l1 = 1.0f - __builtin_amdgcn_logf(P + Q);
+  acc.p = __builtin_fmaf(P, lp + l1, acc.p);
+  acc.q = __builtin_fmaf(Q, lq + l1, acc.q);
+}
+// The terms of one vector of each view, summed on their own first.
+template <int VE, class EA, class EB>
+DEV void jsd_vec(JsdAcc& acc, const JsdConst& k, EA&& xa, EB&& xb) {
+  JsdAcc v{0.0f, 0.0f};
+  #pragma unroll
+  for (int e = 0; e < VE; ++e) jsd_add(v, xa(e), xb(e), k);
+  acc.p += v.p;
+  acc.q += v.q;
+}
+DEV float jsd_sum(const JsdAcc& acc, const JsdConst& k) { return __builtin_fmaf(acc.p, k.sa, acc.q * k.sb); }
 // log2 of a positive double to ~1e-7 absolute: exact exponent split plus the
 // hardware log2 of the mantissa.
 DEV double log2_dbl(double x) {

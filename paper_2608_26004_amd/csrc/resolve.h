@@ -34,8 +34,8 @@ DEV ResidConst resid_const(const KArgs& A, const uint32_t* cst) {
                     __uint_as_float(cst[D_ISF]), __uint_as_float(cst[D_RQ]), __uint_as_float(cst[D_ISQ])};
 }
 DEV JsdConst jsd_const(const uint32_t* cst) {
-  return JsdConst{__uint_as_float(cst[D_RA]), __uint_as_float(cst[D_RB]), __uint_as_float(cst[D_KAHI]),
-                  __uint_as_float(cst[D_KALO]), __uint_as_float(cst[D_KBHI]), __uint_as_float(cst[D_KBLO])};
+  return JsdConst{__uint_as_float(cst[D_JLA]), __uint_as_float(cst[D_JLB]), __uint_as_float(cst[D_JSA]),
+                  __uint_as_float(cst[D_JSB])};
 }
 
 // ------------------------------------------------------------------ decide
@@ -60,14 +60,11 @@ DEV void classify_row(const KArgs& A, const RowGeo& g, const Gather& gq, float M
   double thr = 0.0;
   v[D_C] = __float_as_uint(g.c);
   if (draft) {
-    const double ka = log2_dbl(Sp[sA]), kb = log2_dbl(Sp[sB]);
-    const float kahi = (float)ka, kbhi = (float)kb;
-    v[D_RA] = __float_as_uint(R[sA]);
-    v[D_RB] = __float_as_uint(R[sB]);
-    v[D_KAHI] = __float_as_uint(kahi);
-    v[D_KALO] = __float_as_uint((float)(ka - (double)kahi));
-    v[D_KBHI] = __float_as_uint(kbhi);
-    v[D_KBLO] = __float_as_uint((float)(kb - (double)kbhi));
+    const JsdConst jk = jsd_make(L2[sA], L2[sB]);
+    v[D_JLA] = __float_as_uint(jk.La);
+    v[D_JLB] = __float_as_uint(jk.Lb);
+    v[D_JSA] = __float_as_uint(jk.sa);
+    v[D_JSB] = __float_as_uint(jk.sb);
     const float fd = fuse_masked(gq.t, gq.a, gq.b, A.beta, A.delta_mode);
     // gates whose D is known here, so that the row is decided at once:
     // lambda (App. B), D = lambda * Delta(d), Delta the drafter views'
@@ -511,7 +508,7 @@ DEV uint32_t load_decision(const KArgs& A, int req, Smem& sm) {
 // a and a's vectors stand in for it (such a row has no divergence task).
 template <int DT, int kMode, int DM, bool kNb, bool kResOnly = false, int kGF = 4>
 DEV void pass2_sums(const KArgs& A, const RowGeo& g, long long rel0, int nk, bool dj_in, bool dr_in, bool db_in,
-                    const ResidConst& rk, const JsdConst& jk, float& accj, float (&seg)[kSegPerLane]) {
+                    const ResidConst& rk, const JsdConst& jk, JsdAcc& accj, float (&seg)[kSegPerLane]) {
   constexpr int VE = Elem<DT>::VE;
   constexpr int kG = kMode == 2 ? 1 : kGF;    // vectors per group
   // kResOnly: the row's only task is the residual (the usual emitting row),
@@ -548,19 +545,9 @@ DEV void pass2_sums(const KArgs& A, const RowGeo& g, long long rel0, int nk, boo
       if (!kNb) vb[k] = va[k];
       // each task's element terms under its own (uniform) branch, so that a
       // row without a task never evaluates that task's terms
-      if (dj) {
-        float vj[VE];
-        #pragma unroll
-        for (int e = 0; e < VE; ++e) {
-          const float xa = Elem<DT>::get(va[k], e), xb = Elem<DT>::get(vb[k], e);
-          vj[e] = jsd_elem(xa, xb, jk);
-        }
-        #pragma unroll
-        for (int st = 1; st < VE; st <<= 1)
-          #pragma unroll
-          for (int e = 0; e + st < VE; e += 2 * st) vj[e] += vj[e + st];
-        accj += vj[0];
-      }
+      if (dj)
+        jsd_vec<VE>(accj, jk, [&](int e) { return Elem<DT>::get(va[k], e); },
+                    [&](int e) { return Elem<DT>::get(vb[k], e); });
       if (dr || db) {
         float vr[VE];
         #pragma unroll
@@ -584,7 +571,7 @@ DEV void pass2_sums(const KArgs& A, const RowGeo& g, long long rel0, int nk, boo
 
 template <int DT, int DM, bool kNb, int kGF>
 DEV void pass2_sums_any(const KArgs& A, const RowGeo& g, long long rel0, int nk, long long c0, long long c1,
-                        bool dj, bool dr, bool db, const ResidConst& rk, const JsdConst& jk, float& accj,
+                        bool dj, bool dr, bool db, const ResidConst& rk, const JsdConst& jk, JsdAcc& accj,
                         float (&seg)[kSegPerLane]) {
   constexpr int VE = Elem<DT>::VE;
   if (has_tail(A, c0, c1))
@@ -599,6 +586,79 @@ DEV void pass2_sums_any(const KArgs& A, const RowGeo& g, long long rel0, int nk,
     pass2_sums<DT, 1, DM, kNb, false, kGF>(A, g, rel0, nk, dj, dr, db, rk, jk, accj, seg);
 }
 
+// The divergence of the rows in jm, which have no other task: their vectors
+// form one sequence, row after row, and the next group of a and b is in flight
+// while the current one is reduced; a row's partial costs one wave reduction
+// and all rows share one barrier.  kG vectors per group.  (One row after another
+// waited for each row's loads, reduced the unused weight sums and took two
+// barriers a row: B = 128, K = 6, V = 151936 with the gate output 216 us against
+// 206, a greedy B = 8, K = 2 call 23.1 against 21.4.)
+template <int DT, int kG>
+DEV void pass2_jsd(const KArgs& A, int req, int m, int part, int nk, unsigned long long jm, Smem& sm) {
+  constexpr int VE = Elem<DT>::VE;
+  const int lane = lane_id(), w = wave_id();
+  const long long pbase = (long long)m * kChunkVec + (long long)part * (kChunkVec / A.P2);
+  const long long rel0 = pbase + (long long)w * 64 * nk + lane;
+  auto issue = [&](int i, int k0, u4 (&va)[kG], u4 (&vb)[kG]) {
+    const RowGeo g = row_span<DT>(A, req * (A.K + 1) + i);
+    const __amdgpu_buffer_rsrc_t ra = row_rsrc(A, A.a, g), rb = row_rsrc(A, A.b, g);
+    #pragma unroll
+    for (int k = 0; k < kG; ++k) {
+      const uint32_t off = (uint32_t)((rel0 + (long long)(k0 + k) * 64) * 16);
+      va[k] = buf_load_nt(ra, off);
+      vb[k] = buf_load_nt(rb, off);
+    }
+  };
+  u4 va[kG], vb[kG], na[kG], nb[kG];
+  int i = __builtin_ctzll(jm), k0 = 0;
+  unsigned long long rest = jm & (jm - 1);
+  issue(i, k0, va, vb);
+  JsdAcc acc{0.0f, 0.0f};
+  for (;;) {
+    const bool last = k0 + kG >= nk;
+    const int i2 = !last ? i : (rest != 0 ? __builtin_ctzll(rest) : -1), k2 = last ? 0 : k0 + kG;
+    if (i2 >= 0) issue(i2, k2, na, nb);
+    const RowGeo g = row_span<DT>(A, req * (A.K + 1) + i);
+    const long long c0 = g.vbeg + pbase, c1 = c0 + kChunkVec / A.P2;
+    if (c0 * VE < g.e0 || c1 * VE > g.e0 + A.V) {
+      // the row's first or last part: the array's end is read again element
+      // by element, elements outside the row are masked
+      #pragma unroll
+      for (int k = 0; k < kG; ++k) {
+        const long long vi = g.vbeg + rel0 + (long long)(k0 + k) * 64;
+        fix_vec<DT>(A, g, A.a, vi, va[k]);
+        fix_vec<DT>(A, g, A.b, vi, vb[k]);
+      }
+    }
+    const JsdConst jk = jsd_const(sm.rows[i]);
+    #pragma unroll
+    for (int k = 0; k < kG; ++k)
+      jsd_vec<VE>(acc, jk, [&](int e) { return Elem<DT>::get(va[k], e); },
+                  [&](int e) { return Elem<DT>::get(vb[k], e); });
+    if (last) {
+      const float wj = wave_sum(jsd_sum(acc, jk));
+      if (lane == 0) sm.dm[i][w] = wj;
+      acc = JsdAcc{0.0f, 0.0f};
+      rest &= rest - 1;
+    }
+    if (i2 < 0) break;
+    i = i2;
+    k0 = k2;
+    #pragma unroll
+    for (int k = 0; k < kG; ++k) {
+      va[k] = na[k];
+      vb[k] = nb[k];
+    }
+  }
+  __syncthreads();
+  if (w == 0 && ((jm >> lane) & 1ull) != 0) {
+    float v = 0.0f;
+    #pragma unroll
+    for (int q = 0; q < kWaves; ++q) v += sm.dm[lane][q];
+    st_tag(p2_rec(A, req, lane, m) + P2_J + part, __float_as_uint(v), A.epoch);
+  }
+}
+
 template <int DT, int DM>
 DEV void pass2_item(const KArgs& A, int req, int sub, Smem& sm) {
   const int lane = lane_id(), w = wave_id();
@@ -611,6 +671,14 @@ DEV void pass2_item(const KArgs& A, int req, int sub, Smem& sm) {
   unsigned long long tmask = (unsigned long long)sm.req[R_TASK_LO] | ((unsigned long long)sm.req[R_TASK_HI] << 32);
   // only rows 0..K of the request (K + 1 <= 64)
   if (A.K + 1 < 64) tmask &= (1ull << (A.K + 1)) - 1ull;
+  // the rows whose only task is their divergence
+  const unsigned long long jm = __ballot(lane <= A.K && sm.rows[lane][D_TASK] == (uint32_t)kTaskJsd) & tmask;
+  if (jm != 0) {
+    if (nk >= 4) pass2_jsd<DT, 4>(A, req, m, part, nk, jm, sm);
+    else if (nk >= 2) pass2_jsd<DT, 2>(A, req, m, part, nk, jm, sm);
+    else pass2_jsd<DT, 1>(A, req, m, part, nk, jm, sm);
+    tmask &= ~jm;
+  }
   while (tmask != 0) {
     const int i = __builtin_ctzll(tmask);
     tmask &= tmask - 1;
@@ -622,7 +690,8 @@ DEV void pass2_item(const KArgs& A, int req, int sub, Smem& sm) {
     const JsdConst jk = jsd_const(cst);
     const long long rel0 = pbase + (long long)w * 64 * nk + lane;
     const long long c0 = g.vbeg + pbase, c1 = c0 + kChunkVec / A.P2;
-    float accj = 0.0f, seg[kSegPerLane];
+    JsdAcc accj{0.0f, 0.0f};
+    float seg[kSegPerLane];
     #pragma unroll
     for (int k = 0; k < kSegPerLane; ++k) seg[k] = 0.0f;
     if (task != 0) {
@@ -652,7 +721,7 @@ DEV void pass2_item(const KArgs& A, int req, int sub, Smem& sm) {
     uint64_t* rec = p2_rec(A, req, i, m);
     if (lane < nk)
       st_tag(rec + P2_SEG + part * (kSubPerChunk / A.P2) + w * nk + lane, __float_as_uint(mine), A.epoch);
-    const float wj = wave_sum(accj);
+    const float wj = wave_sum(jsd_sum(accj, jk));
     if (lane == 0) sm.wj[w] = wj;
     __syncthreads();
     if (threadIdx.x == 0) {

@@ -573,9 +573,9 @@ void xv_pass2_kernel(KArgs A, XArgs X) {
     #pragma unroll
     for (int k = 0; k < kXBatch; ++k) en[k] = xv_entry(it, pa + k * 64 + lane);
     const uint64_t* blk = dec_row(A, it.req, it.i);
-    uint32_t cst[D_KBLO + 1];
+    uint32_t cst[D_JSB + 1];
     #pragma unroll
-    for (int k = 0; k <= D_KBLO; ++k) cst[k] = pay(blk[k]);
+    for (int k = 0; k <= D_JSB; ++k) cst[k] = pay(blk[k]);
     const uint32_t task = cst[D_TASK];
     const bool dj = (task & kTaskJsd) != 0u, dr = (task & kTaskRes) != 0u, db = (task & kTaskBonus) != 0u;
     const ResidConst rk = resid_const(A, cst);
@@ -591,7 +591,8 @@ void xv_pass2_kernel(KArgs A, XArgs X) {
     float* sums = X.sums + ((size_t)it.row * X.T + tile) * X.nsub;
     int cur = u0 * kXSubPerUnit;
     const int send = u1 * kXSubPerUnit;
-    float accj = 0.0f, acc = 0.0f;
+    JsdAcc accj{0.0f, 0.0f};
+    float acc = 0.0f;
     for (int p0 = pa; p0 < pe; p0 += 64 * kXBatch) {
       float xt[kXBatch];
       int x[kXBatch];
@@ -609,7 +610,8 @@ void xv_pass2_kernel(KArgs A, XArgs X) {
         const bool in = p0 + k * 64 + lane < pe;
         if (p0 + k * 64 >= pe) break;
         const float xa = XT::a(pr[k]), xb = XT::b(pr[k]);
-        if (dj) accj += in ? jsd_elem(xa, xb, jk) : 0.0f;
+        // (masked: no mass in either view)
+        if (dj) jsd_add(accj, in ? xa : -INFINITY, in ? xb : -INFINITY, jk);
         if (dr || db) {
           float v = dr ? resid_elem<DM>(xt[k], xa, xb, rk) : bonus_elem(xt[k], rk.c, rk.Rf);
           v = in ? v : 0.0f;
@@ -635,7 +637,7 @@ void xv_pass2_kernel(KArgs A, XArgs X) {
       }
     }
     if (dj) {
-      const float wj = wave_sum(accj);
+      const float wj = wave_sum(jsd_sum(accj, jk));
       if (lane == 0) sm.wj[w] = wj;
       __syncthreads();
       if (threadIdx.x == 0) {

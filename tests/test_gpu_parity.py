@@ -53,6 +53,31 @@ def test_pass2_parts(gpu, B):
             _note(compare(x, g, gate_mode=mode, label=f"pass-2 parts B={B} mode={mode} gate={want_gate}"))
 
 
+@pytest.mark.parametrize("dtype,B,K,V", [
+    ("bf16", 1, 1, 1), ("bf16", 2, 3, 2047), ("bf16", 3, 5, 16385), ("bf16", 5, 2, 50257),
+    ("fp32", 3, 3, 8193), ("fp32", 7, 2, 50257), ("bf16", 90, 2, 120001)])
+def test_divergence_rows(gpu, dtype, B, K, V):
+    """Rows whose only second-pass task is their divergence (greedy requests
+    with the gate output), summed row after row with the next vectors in
+    flight: chunks split in 8, 4 and 2 parts, rows that start mid-vector, the
+    array's last partial vector, tokens that both views or the full view
+    alone mask, logits far from 0, and rows whose views agree in between."""
+    x = synth.generate(B=B, K=K, V=V, dtype=dtype, rho=("alternate", 1.5, 0.0), tau=("alternate", 0.0, 0.0),
+                       seed=V % 991 + K)
+    if V > 1000:
+        neg = np.float32(-np.inf) if dtype == "fp32" else np.uint16(0xFF80)
+        x.a[:, :, 100:140] = neg
+        x.b[:, :, 100:120] = neg
+        if dtype == "fp32":
+            x.a[0] += np.float32(37.0)
+            x.b[0] += np.float32(37.0)
+        # the drafts keep their mass
+        x.draft_tokens[:] = np.where((x.draft_tokens >= 100) & (x.draft_tokens < 140), 7, x.draft_tokens)
+    for mode in (0, 1):
+        g = run_gpu(x, gate_mode=mode)
+        _note(compare(x, g, gate_mode=mode, label=f"divergence rows {dtype} B={B} K={K} V={V} mode={mode}"))
+
+
 def test_argmax_ties_across_waves_and_chunks(gpu):
     """Greedy rows whose fused maximum is attained twice, in the runs of two
     waves of one statistics item and in two chunks: the first index wins
