@@ -741,22 +741,37 @@ constexpr int kPickRun = 8;
 // Where a cross-family call's pass-2 kernel left its sums: [rows][T][nsub]
 // weight sums and [rows][T] divergence partials, T tiles per row, written by
 // an earlier kernel (no tags); a sub-block is kXSub consecutive tokens.
-struct XPass2 { const float* sums; const float* jpart; int T, nsub; };
+struct XPass2 { float* sums; const float* jpart; int T, nsub; };
 
-// The sums of sub-blocks [s0, s0 + n) of row `row` of a cross-family call,
-// each over the row's tiles in order; the other entries of v are zero.
+// The sums of row `row`'s sub-blocks, each over the row's tiles in order, into
+// the row's first tile.  Whole workgroup, a thread per sub-block: consecutive
+// threads read consecutive sums, kPickTiles tiles at once.  (One wave reading
+// runs of kPickRun sub-blocks per lane, tile after tile, took most of a small call with
+// many tiles: B = 2, K = 4, V = 256000 fp32, 32 tiles.)
+constexpr int kPickTiles = 16;
+DEV void fold_sub_tiles(const XPass2& xp, size_t row) {
+  float* p = xp.sums + row * xp.T * xp.nsub;
+  for (int s = wave_id() * 64 + lane_id(); s < xp.nsub; s += kThreads) {
+    float acc = 0.0f;
+    for (int t0 = 0; t0 < xp.T; t0 += kPickTiles) {
+      float v[kPickTiles];
+      #pragma unroll
+      for (int k = 0; k < kPickTiles; ++k) v[k] = p[(size_t)min(t0 + k, xp.T - 1) * xp.nsub + s];
+      #pragma unroll
+      for (int k = 0; k < kPickTiles; ++k) acc += t0 + k < xp.T ? v[k] : 0.0f;
+    }
+    p[s] = acc;
+  }
+  __syncthreads();
+}
+// Sub-blocks [s0, s0 + n) of the folded sums; the other entries of v are zero.
 DEV void load_sub_tiles(const XPass2& xp, size_t row, int s0, int n, float (&v)[kPickRun]) {
-  #pragma unroll
-  for (int j = 0; j < kPickRun; ++j) v[j] = 0.0f;
   // (a lane without sub-blocks reads the row's first and drops them)
   const float* p = xp.sums + row * xp.T * xp.nsub;
-  #pragma unroll 4
-  for (int t = 0; t < xp.T; ++t) {
-    #pragma unroll
-    for (int j = 0; j < kPickRun; ++j) {
-      const float x = p[(size_t)t * xp.nsub + (j < n ? s0 + j : 0)];
-      v[j] += j < n ? x : 0.0f;
-    }
+  #pragma unroll
+  for (int j = 0; j < kPickRun; ++j) {
+    const float x = p[j < n ? s0 + j : 0];
+    v[j] = j < n ? x : 0.0f;
   }
 }
 
@@ -801,6 +816,7 @@ template <int DT, int DM, bool kXv>
 DEV int cdf_pick(const KArgs& A, int req, int i, double u, bool bonus, Smem& sm, bool& ok, const XPass2& xp) {
   constexpr int VE = kXv ? 8 : Elem<DT>::VE;
   const int lane = lane_id(), w = wave_id();
+  if (kXv) fold_sub_tiles(xp, (size_t)(req * (A.K + 1) + i));
   if (w == 0) {
     const RowGeo g = row_span<DT>(A, req * (A.K + 1) + i);
     const int nsub = kXv ? xp.nsub : A.S * kSubPerChunk;
