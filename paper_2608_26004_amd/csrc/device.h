@@ -490,6 +490,12 @@ DEV int row16_or(int x) {
   x |= ror16_i<2>(x);
   return x | ror16_i<1>(x);
 }
+DEV int row16_add(int x) {
+  x += ror16_i<8>(x);
+  x += ror16_i<4>(x);
+  x += ror16_i<2>(x);
+  return x + ror16_i<1>(x);
+}
 DEV double row16_sum(double x) {
   x += ror16_d<8>(x);
   x += ror16_d<4>(x);

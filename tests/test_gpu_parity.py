@@ -504,6 +504,22 @@ def test_xvocab_tile_edges(gpu, dtype, V, Vd, frac):
     assert np.array_equal(e[2][read], g[2][read]) and read[:, 0].all() and read[:, x.K].all()
 
 
+@pytest.mark.parametrize("dtype,V,Vd,frac", [
+    ("bf16", 3000, 15 * 16384, 0.9), ("bf16", 2049, 16 * 16384, 1.0), ("bf16", 140001, 16 * 16384 + 1, 0.6),
+    ("fp32", 132097, 33 * 8192 - 1, 0.5)])
+def test_xvocab_many_tiles(gpu, dtype, V, Vd, frac):
+    """15, 16, 17 and 33 tiles a row (the list kernel sums 16 tiles at once,
+    the pick folds 16 at once) and verifier vocabularies of 3, 3, 137 and 130
+    units of the lists (128 counts at once); the emission draws go through
+    the folded sums."""
+    from parity_util import make_xvocab
+    x = synth.generate(B=3, K=2, V=V, dtype=dtype, rho=("alternate", 0.7, 0.0),
+                       tau=("alternate", 0.9, 0.0), seed=V % 1009)
+    ad, bd, vm, mx = make_xvocab(x, Vd, frac, seed=Vd % 97)
+    g = run_gpu(mx, vocab=(ad, bd, vm))
+    _note(compare(mx, g, label=f"xvocab many tiles {dtype} V={V} Vd={Vd}"))
+
+
 # ----------------------------------------------------------- early exit --
 def _check_early_exit(x, ee, **kw):
     """Early exit against the full read of the same call (same kernels on
