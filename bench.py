@@ -234,7 +234,7 @@ def main():
                     help="source of delta in f = t + beta delta (a-b: the paper's)")
     ap.add_argument("--lam", type=float, default=0.1, help="scale of the lambda gate")
     ap.add_argument("--full", action="store_true",
-                    help="also write the full [B, K+1, V] fp32 log-probability rows (second kernel)")
+                    help="also write the full [B, K+1, V] fp32 log-probability rows")
     ap.add_argument("--xvocab", type=str, default=None, metavar="VD:SHARED",
                     help="cross-family drafter: vocabulary size and shared tokens, e.g. 128256:109566")
     ap.add_argument("--early-exit", type=int, default=0, metavar="ROWS",
@@ -377,8 +377,11 @@ def main():
     rows = B * (K + 1)
     nbytes = x.nbytes_read(args.fuse_bonus) if xv_bytes is None else xv_bytes
     if args.full:
-        # the second kernel reads the rows again and writes 4 bytes per element
-        nbytes += x.nbytes_read(args.fuse_bonus) + 4 * B * (K + 1) * V
+        # 4 bytes written per element; with the KL gate and for cross-family
+        # calls a second kernel reads the rows again
+        nbytes += 4 * B * (K + 1) * V
+        if xv_bytes is not None or args.gate_mode == "kl":
+            nbytes += x.nbytes_read(args.fuse_bonus)
     achieved = nbytes / (kern_ms * 1e-3) / 1e9
 
     if args.calibrate_copy:
