@@ -16,6 +16,7 @@
 #define DEV __device__ __forceinline__
 #define ASYM_HD __host__ __device__
 #include "schedule.h"
+#include "xmap.h"
 
 namespace asym {
 
@@ -836,11 +837,6 @@ DEV void fix_vec(const KArgs& A, const RowGeo& g, const void* src, long long vi,
 // portability"): the drafter logits of verifier token x are a[vmap[x]] and
 // b[vmap[x]]; a verifier token without a shared counterpart cannot be
 // committed, so it counts as masked in every view (t = a = b = -inf).
-DEV int map_id(const KArgs& A, long long x) {
-  if (x < 0 || x >= A.V) return -1;
-  const int j = A.vmap[x];
-  return (j >= 0 && j < A.Vd) ? j : -1;
-}
 // The vector vi of row g in the verifier's layout: vt (loaded and repaired)
 // gets -inf where the token is not shared, and, when ab, va and vb are
 // gathered from the drafter rows through the map (-inf where not shared).
@@ -848,16 +844,15 @@ template <int DT>
 DEV void map_vecs(const KArgs& A, const RowGeo& g, long long vi, u4& vt, u4& va, u4& vb, bool ab) {
   constexpr int VE = Elem<DT>::VE;
   u4 t2 = {0, 0, 0, 0}, a2 = t2, b2 = t2;
-  const long long dbase = (long long)g.row * A.Vd;
   #pragma unroll
   for (int e = 0; e < VE; ++e) {
-    const int j = map_id(A, vi * VE + e - g.e0);
+    const XPlace pl = map_place(A.vmap, g.row, A.V, A.Vd, vi * VE + e - g.e0, ab);
     float xt = -INFINITY, xa = -INFINITY, xb = -INFINITY;
-    if (j >= 0) {
+    if (pl.in) {
       xt = Elem<DT>::get(vt, e);
       if (ab) {
-        xa = Elem<DT>::load_one(A.a, dbase + j);
-        xb = Elem<DT>::load_one(A.b, dbase + j);
+        xa = Elem<DT>::load_one(A.a, pl.ab);
+        xb = Elem<DT>::load_one(A.b, pl.ab);
       }
     }
     Elem<DT>::put_one(t2, e, xt);
@@ -867,18 +862,18 @@ DEV void map_vecs(const KArgs& A, const RowGeo& g, long long vi, u4& vt, u4& va,
   vt = t2;
   if (ab) { va = a2; vb = b2; }
 }
-// The three logits of verifier token x (0 <= x < V) of row g, mapped.
+// The emission logit of verifier token x of row g: the fused logit (-inf where
+// it is not a number), or t on a plain bonus row, which reads neither a nor b (a
+// call without drafts may bring none).
 template <int DT>
-DEV void mapped_tab(const KArgs& A, const RowGeo& g, int x, float& t, float& a, float& b) {
-  const int j = A.vmap != nullptr ? map_id(A, x) : ((x >= 0 && x < A.V) ? x : -1);
-  if (j < 0) {
-    t = a = b = -INFINITY;
-    return;
-  }
-  t = Elem<DT>::load_one(A.t, g.e0 + x);
-  const long long d = A.vmap != nullptr ? (long long)g.row * A.Vd + j : g.e0 + x;
-  a = Elem<DT>::load_one(A.a, d);
-  b = Elem<DT>::load_one(A.b, d);
+DEV float emit_logit(const KArgs& A, const RowGeo& g, int x, bool bonus) {
+  XPlace pl{x >= 0 && x < A.V, 0, 0};
+  if (A.vmap != nullptr) pl = map_place(A.vmap, g.row, A.V, A.Vd, x, !bonus);
+  else pl.t = pl.ab = g.e0 + x;
+  if (!pl.in) return -INFINITY;
+  const float t = Elem<DT>::load_one(A.t, pl.t);
+  if (bonus) return t;
+  return fuse_masked(t, Elem<DT>::load_one(A.a, pl.ab), Elem<DT>::load_one(A.b, pl.ab), A.beta, A.delta_mode);
 }
 
 // Draft-token gathers of one row through the scalar cache (wave-uniform

@@ -883,19 +883,24 @@ DEV int cdf_pick(const KArgs& A, int req, int i, double u, bool bonus, Smem& sm,
         long long first;                     // flat index of the lane's first element
         if constexpr (kXv) {
           const int x0 = sel * 64 * VE + lane * VE;
+          XPlace pl[VE];
           first = g.e0 + x0;
           #pragma unroll
           for (int e = 0; e < VE; ++e) {
-            // (loads without branches: token 0 and drafter id 0 exist)
-            const int j = A.vmap[x0 + e < A.V ? x0 + e : 0];
-            const bool in = x0 + e < A.V && j >= 0 && j < A.Vd;
-            const long long jd = (long long)g.row * A.Vd + (in ? j : 0);
-            xt[e] = Elem<DT>::load_one(A.t, g.e0 + (in ? x0 + e : 0));
-            xa[e] = Elem<DT>::load_one(A.a, jd);
-            xb[e] = Elem<DT>::load_one(A.b, jd);
-            xt[e] = in ? xt[e] : -INFINITY;
-            xa[e] = in ? xa[e] : -INFINITY;
-            xb[e] = in ? xb[e] : -INFINITY;
+            pl[e] = map_place(A.vmap, g.row, A.V, A.Vd, x0 + e, !bonus);
+            xt[e] = Elem<DT>::load_one(A.t, pl[e].t);
+            xt[e] = pl[e].in ? xt[e] : -INFINITY;
+            xa[e] = xb[e] = -INFINITY;
+          }
+          // a plain bonus row draws from t alone
+          if (!bonus) {
+            #pragma unroll
+            for (int e = 0; e < VE; ++e) {
+              xa[e] = Elem<DT>::load_one(A.a, pl[e].ab);
+              xb[e] = Elem<DT>::load_one(A.b, pl[e].ab);
+              xa[e] = pl[e].in ? xa[e] : -INFINITY;
+              xb[e] = pl[e].in ? xb[e] : -INFINITY;
+            }
           }
         } else {
           const int ch = sel / kSubPerChunk, sub = sel % kSubPerChunk;
@@ -972,16 +977,14 @@ DEV int cdf_pick(const KArgs& A, int req, int i, double u, bool bonus, Smem& sm,
   return sm.flags[3];
 }
 
-// Argmax of the fused logits of a row by a full scan (whole workgroup); only
+// Argmax of the emission logits of a row by a full scan (whole workgroup); only
 // used when a residual is empty (p~ equal to q in fp32).
 template <int DT>
-DEV int row_argmax_f(const KArgs& A, const RowGeo& g, Smem& sm) {
+DEV int row_argmax(const KArgs& A, const RowGeo& g, bool bonus, Smem& sm) {
   float best = kFloorM;
   int bi = 0x7FFFFFFF;
   for (int x = wave_id() * 64 + lane_id(); x < A.V; x += kThreads) {
-    float xt, xa, xb;
-    mapped_tab<DT>(A, g, x, xt, xa, xb);
-    const float f = fuse_rt(xt, xa, xb, A.beta, A.delta_mode);
+    const float f = emit_logit<DT>(A, g, x, bonus);
     if (f > best) { best = f; bi = x; }
   }
   const float M = wave_max(best);
@@ -1068,16 +1071,9 @@ DEV void pick_item(const KArgs& A, int req, Smem& sm, const XPass2& xp = XPass2{
     int pick = cdf_pick<DT, DM, kXv>(A, req, j, u, bonus, sm, ok, xp);
     const RowGeo g = row_span<DT>(A, req * (K + 1) + j);
     const bool have_x = pick >= 0 && sm.flags[2] != 0;
-    if (pick < 0) pick = row_argmax_f<DT>(A, g, sm);
+    if (pick < 0) pick = row_argmax<DT>(A, g, bonus, sm);
     next = pick;
-    float x;
-    if (have_x) {
-      x = (float)sm.dd[3];
-    } else {
-      float xa, xb;
-      mapped_tab<DT>(A, g, next, x, xa, xb);
-      if (!bonus) x = fuse_masked(x, xa, xb, A.beta, A.delta_mode);
-    }
+    const float x = have_x ? (float)sm.dd[3] : emit_logit<DT>(A, g, next, bonus);
     const double c = (double)__uint_as_float(sm.rows[j][D_C]);
     const double l2 = u2d(sm.rows[j][D_L2E_LO], sm.rows[j][D_L2E_HI]);
     lpn = (float)(((double)x * c - l2) * kLn2);

@@ -520,6 +520,37 @@ def test_xvocab_many_tiles(gpu, dtype, V, Vd, frac):
     _note(compare(mx, g, label=f"xvocab many tiles {dtype} V={V} Vd={Vd}"))
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+@pytest.mark.parametrize("V,Vd", [(7, 50000), (1, 3), (700, 9001)])
+def test_xvocab_without_drafts(gpu, dtype, V, Vd):
+    """K = 0, a plain bonus row drawn from t alone, a drafter vocabulary longer
+    than the verifier's, and no a and b at all (NULL through the C ABI): the
+    tokens are the oracle's, and the same as with drafter rows given."""
+    import ctypes
+    import paper_2608_26004_amd as asp
+    import torch
+    from parity_util import make_xvocab, to_device
+    x = synth.generate(B=6, K=0, V=V, dtype=dtype, rho=1.0, tau=("alternate", 0.8, 0.0), seed=V + 3)
+    ad, bd, vm, mx = make_xvocab(x, Vd, 0.9, seed=5)
+    g = run_gpu(mx, vocab=(ad, bd, vm), want_gate=False)
+    _note(compare(mx, g, label=f"xvocab K=0 {dtype} V={V} Vd={Vd}"))
+    lib, dev = asp.load_library(), torch.device("cuda")
+    dt = asp.BF16 if dtype == "bf16" else asp.FP32
+    t, u, tau, m = (to_device(v) for v in (mx.t, mx.uniforms, mx.temperature, vm))
+    ws = torch.zeros(lib.asymspec_workspace_size_xvocab(x.B, 0, V, Vd, dt), dtype=torch.uint8, device=dev)
+    acc, nxt = (torch.full((x.B,), -7, dtype=torch.int32, device=dev) for _ in range(2))
+    flp = torch.zeros(x.B, 1, device=dev)
+    p = lambda v: ctypes.c_void_p(v.data_ptr())     # noqa: E731
+    params = asp._Params(1.0, 0.5, asp.GATE_CDA, 0, asp.DELTA_AB, 0.1, 0)
+    st = lib.asymspec_fuse_verify_xvocab(p(t), None, None, dt, p(m), Vd, None, None, p(u), p(tau), x.B, 0, V,
+                                         ctypes.byref(params), p(acc), p(nxt), p(flp), None, None, p(ws),
+                                         ws.numel(), ctypes.c_void_p(torch.cuda.current_stream(dev).cuda_stream))
+    assert st == asp.OK, asp.status_string(st)
+    torch.cuda.synchronize()
+    assert np.array_equal(acc.cpu().numpy(), g[0]) and np.array_equal(nxt.cpu().numpy(), g[1])
+    assert np.array_equal(flp.cpu().numpy(), g[2])
+
+
 # ----------------------------------------------------------- early exit --
 def _check_early_exit(x, ee, **kw):
     """Early exit against the full read of the same call (same kernels on
