@@ -20,7 +20,8 @@
 // system-scope atomics (no cache flushes).  An aligned 64-bit access is
 // single-copy atomic, so a reader that sees the epoch in a slot sees its
 // payload; writers never wait, readers poll until every slot they need is
-// in.  The workspace therefore needs no initialisation.
+// in.  The workspace therefore needs no initialisation, and what a call of
+// another shape or kind left in it cannot pass for a slot (tags.h).
 
 #include <hip/hip_runtime.h>
 
@@ -210,9 +211,7 @@ static uint32_t next_epoch() {
     // library instance is unlikely to hold slots tagged with a live epoch
     ctr.store((uint32_t)((t ^ (t >> 32) ^ ((uint64_t)getpid() << 16)) & 0x3FFFFFFFu) | 1u);
   });
-  uint32_t e;
-  do { e = ctr.fetch_add(1u); } while (e == 0u);
-  return e;
+  return epoch_of(ctr.fetch_add(1u));
 }
 
 static bool aligned(const void* p, size_t a) { return ((uintptr_t)p % a) == 0; }

@@ -16,6 +16,7 @@
 #define DEV __device__ __forceinline__
 #define ASYM_HD __host__ __device__
 #include "schedule.h"
+#include "tags.h"
 #include "xmap.h"
 
 namespace asym {

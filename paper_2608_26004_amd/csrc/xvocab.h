@@ -40,17 +40,15 @@ constexpr int kXSub = 512;            // verifier tokens per pass-2 sub-block (8
 constexpr int kXSubPerUnit = kXUnit / kXSub;
 constexpr int kXBatch = 8;            // entries per thread and step
 
-// A list entry holds the drafter id within its tile (low kJBits bits) and the
-// low bits of the verifier token; the token's high bits follow from the
-// entry's place in the list (the unit index).
 constexpr int x_log2(int n) { return n <= 1 ? 0 : 1 + x_log2(n / 2); }
 template <int DT> struct XTileBase {
   static constexpr int kBytes = 65536;
   static constexpr int kThr = 512;
   static constexpr int kWv = kThr / 64;
   static constexpr int kN = kBytes / (DT == ASYMSPEC_BF16 ? 4 : 8);   // drafter ids per tile
-  static constexpr int kJBits = x_log2(kN);
-  static constexpr int kXBits = 32 - kJBits;
+  using Entry = XEntry<x_log2(kN)>;
+  static constexpr int kSpan = (int)Entry::kSpan;
+  static_assert(kSpan % kXUnit == 0, "a span of tokens ends with a unit of the lists");
   static constexpr int kVec = kN / (DT == ASYMSPEC_BF16 ? 8 : 4) / kThr;   // staged vectors per thread and stream
 };
 template <int DT> struct XTile;
@@ -171,7 +169,7 @@ __global__ __launch_bounds__(kThreads) void xv_fill_kernel(KArgs A, XArgs X) {
       const uint32_t x = (uint32_t)(u * kXUnit + w * kXPerWave + k * 64 + lane);
       if (in)
         X.list[at + __popcll(m & ((1ull << lane) - 1ull))] =
-            (x << XTile<DT>::kJBits) | (uint32_t)(j[k] - t * XTile<DT>::kN);
+            XTile<DT>::Entry::make(x, (uint32_t)(j[k] - t * XTile<DT>::kN));
       at += __popcll(m);
     }
     start += all[t];
@@ -261,12 +259,13 @@ struct XStage {
   }
 };
 
-// One tile of one row: its list, the row of t, and where the tokens' high bits
+// One tile of one row: its list, the row of t, and where the tokens' spans
 // change.  Both are read through buffer resources, which return zeros past
 // the list's end without a branch (entry 0 names token 0 and the tile's first
 // slot: both exist).
 struct XItem {
   int row, req, i, tile, n, lead, nhi;
+  int q1;   // list position from which tokens are at kSpan or above
   __amdgpu_buffer_rsrc_t list, t;
 };
 
@@ -283,27 +282,43 @@ DEV XItem xv_item(const KArgs& A, const XArgs& X, int row, int tile) {
   it.n = ix[X.U] - first;
   it.list = make_rsrc(X.list + first, (unsigned long long)it.n * 4);
   it.t = make_rsrc((const char*)A.t + (unsigned long long)row * A.V * ES, (unsigned long long)A.V * ES);
-  it.nhi = (A.V - 1) >> XTile<DT>::kXBits;
+  it.nhi = (A.V - 1) / XTile<DT>::kSpan;
   it.lead = 0;
+  it.q1 = 0x7FFFFFFF;
   return it;
 }
 
-// Thread h fills the list position from which tokens have high bits >= h.
+// Thread h fills the list position from which tokens are at h spans or above
+// (q1 by xv_bounds_in once they are in).
 template <int DT>
 DEV void xv_bounds(const XArgs& X, const XItem& it, XSmem<DT>& sm) {
   const int h = (int)threadIdx.x;
   if (h <= it.nhi && h < 64) {
     const int32_t* ix = X.idx + (size_t)it.tile * (X.U + 1);
-    sm.q[h] = ix[h << (XTile<DT>::kXBits - x_log2(kXUnit))] - ix[0];
+    sm.q[h] = ix[h * (XTile<DT>::kSpan / kXUnit)] - ix[0];
   }
 }
 
-// Verifier token of entry e at list position p.
 template <int DT>
-DEV int xv_token(uint32_t e, int p, const XItem& it, const XSmem<DT>& sm) {
-  uint32_t x = e >> XTile<DT>::kJBits;
-  for (int h = 1; h <= it.nhi; ++h) x += p >= sm.q[h] ? 1u << XTile<DT>::kXBits : 0u;
-  return (int)x;
+DEV void xv_bounds_in(XItem& it, const XSmem<DT>& sm) {
+  if (it.nhi >= 1) it.q1 = __builtin_amdgcn_readfirstlane(sm.q[1]);
+}
+
+// Verifier tokens of the entries en[e] at list positions p0 + e * kStride.
+template <int DT, int kStride>
+DEV void xv_tokens(const XItem& it, const XSmem<DT>& sm, const uint32_t (&en)[kXBatch], int p0, int (&x)[kXBatch]) {
+  constexpr int kHi = XTile<DT>::kSpan;
+  #pragma unroll
+  for (int e = 0; e < kXBatch; ++e) x[e] = (int)XTile<DT>::Entry::token(en[e]);
+  if (it.nhi >= 1) {
+    #pragma unroll
+    for (int e = 0; e < kXBatch; ++e) x[e] += p0 + e * kStride >= it.q1 ? kHi : 0;
+  }
+  for (int h = 2; h <= it.nhi; ++h) {
+    const int q = __builtin_amdgcn_readfirstlane(sm.q[h]);
+    #pragma unroll
+    for (int e = 0; e < kXBatch; ++e) x[e] += p0 + e * kStride >= q ? kHi : 0;
+  }
 }
 
 // Entry at list position p.
@@ -319,7 +334,7 @@ DEV float xv_t(const XItem& it, int x) {
 }
 template <int DT>
 DEV typename XTile<DT>::Pair xv_pair(const XItem& it, const XSmem<DT>& sm, uint32_t e) {
-  return sm.pair[(e & ((1u << XTile<DT>::kJBits) - 1u)) + it.lead];
+  return sm.pair[XTile<DT>::Entry::id(e) + it.lead];
 }
 
 // Tokens and t of the entries en[e] at positions p0 + e * kThr.
@@ -327,12 +342,7 @@ template <int DT>
 DEV void xv_load_t(const XItem& it, const XSmem<DT>& sm, const uint32_t (&en)[kXBatch], int p0, int (&x)[kXBatch],
                    float (&xt)[kXBatch]) {
   using XT = XTile<DT>;
-  #pragma unroll
-  for (int e = 0; e < kXBatch; ++e) x[e] = (int)(en[e] >> XT::kJBits);
-  if (it.nhi > 0) {
-    #pragma unroll
-    for (int e = 0; e < kXBatch; ++e) x[e] = xv_token<DT>(en[e], p0 + e * XT::kThr, it, sm);
-  }
+  xv_tokens<DT, XT::kThr>(it, sm, en, p0, x);
   #pragma unroll
   for (int e = 0; e < kXBatch; ++e) xt[e] = xv_t<DT>(it, x[e]);
 }
@@ -405,6 +415,7 @@ void xv_stats_kernel(KArgs A, XArgs X) {
     if (fused) stg.store(A, sm.pair);
   }
   __syncthreads();
+  xv_bounds_in<DT>(it, sm);
   const float tau = sload_f32(A.tau, it.req);
   const bool samp = tau > 0.0f;
   const float c = samp ? kL2E / tau : kL2E;
@@ -593,6 +604,7 @@ void xv_pass2_kernel(KArgs A, XArgs X) {
     }
     xv_bounds<DT>(X, it, sm);
     __syncthreads();
+    xv_bounds_in<DT>(it, sm);
     float* sums = X.sums + ((size_t)it.row * X.T + tile) * X.nsub;
     int cur = u0 * kXSubPerUnit;
     const int send = u1 * kXSubPerUnit;
@@ -602,9 +614,9 @@ void xv_pass2_kernel(KArgs A, XArgs X) {
       float xt[kXBatch];
       int x[kXBatch];
       typename XT::Pair pr[kXBatch];
+      xv_tokens<DT, 64>(it, sm, en, p0 + lane, x);
       #pragma unroll
       for (int k = 0; k < kXBatch; ++k) {
-        x[k] = xv_token<DT>(en[k], p0 + k * 64 + lane, it, sm);
         xt[k] = dr || db ? xv_t<DT>(it, x[k]) : 0.0f;
         pr[k] = dj || dr ? xv_pair<DT>(it, sm, en[k]) : XT::masked();
       }
@@ -626,7 +638,7 @@ void xv_pass2_kernel(KArgs A, XArgs X) {
           const int last = __builtin_amdgcn_readlane(sub, min(63, pe - 1 - (p0 + k * 64)));
           while (cur < last) {
             const float total = wave_sum(acc + (sub == cur ? v : 0.0f));
-            if (lane == 0) sums[cur] = total;
+            if (lane == 0) sums[cur] = plain_sum(total);
             acc = 0.0f;
             ++cur;
           }
@@ -637,7 +649,7 @@ void xv_pass2_kernel(KArgs A, XArgs X) {
     if (dr || db) {
       for (; cur < send; ++cur) {
         const float total = wave_sum(acc);
-        if (lane == 0) sums[cur] = total;
+        if (lane == 0) sums[cur] = plain_sum(total);
         acc = 0.0f;
       }
     }
@@ -648,7 +660,7 @@ void xv_pass2_kernel(KArgs A, XArgs X) {
       if (threadIdx.x == 0) {
         float v = 0.0f;
         for (int q = 0; q < XT::kWv; ++q) v += sm.wj[q];
-        X.jpart[(size_t)it.row * X.T + tile] = v;
+        X.jpart[(size_t)it.row * X.T + tile] = plain_sum(v);
       }
     }
   }

@@ -488,8 +488,8 @@ def test_xvocab_workload_1(gpu):
 def test_xvocab_tile_edges(gpu, dtype, V, Vd, frac):
     """Drafter vocabularies around a tile (16384 bf16 or 8192 fp32 ids), odd
     ones (rows then start between 4-byte boundaries), verifier vocabularies
-    around a unit of the lists (1024 tokens) and past the token bits that a
-    list entry holds (2^18 or 2^19), and tiles with few or no entries; greedy
+    around a unit of the lists (1024 tokens) and past the tokens that a
+    list entry tells apart (196608 or 393216), and tiles with few or no entries; greedy
     and sampling requests, the divergence of every row, and early exit with
     the full read's outputs."""
     from parity_util import make_xvocab
@@ -549,6 +549,38 @@ def test_xvocab_without_drafts(gpu, dtype, V, Vd):
     torch.cuda.synchronize()
     assert np.array_equal(acc.cpu().numpy(), g[0]) and np.array_equal(nxt.cpu().numpy(), g[1])
     assert np.array_equal(flp.cpu().numpy(), g[2])
+
+
+def test_one_workspace_for_calls_of_every_kind(gpu):
+    """Plain, cross-family and full-row calls of different shapes in turn on
+    one Workspace, three times over: what a call leaves there (list entries,
+    weight sums and divergence partials of a cross-family call among it) is
+    nothing to the next; every call's outputs are the oracle's and no request
+    is marked."""
+    import paper_2608_26004_amd as asp
+    import torch
+    from parity_util import make_xvocab, to_device
+    ws = asp.Workspace(torch.device("cuda"))
+    calls = []
+    for k, (B, K, V, dtype, Vd, full) in enumerate([
+            (6, 3, 40000, "bf16", 50001, False), (6, 3, 40000, "bf16", 0, False), (9, 2, 20000, "bf16", 0, True),
+            (4, 2, 30001, "fp32", 30000, False), (2, 5, 66000, "fp32", 0, False), (12, 1, 5000, "bf16", 7000, True)]):
+        x = synth.generate(B=B, K=K, V=V, dtype=dtype, rho=("alternate", 0.8, 0.0), tau=("alternate", 0.9, 0.0),
+                           seed=40 + k)
+        ad, bd, vm = x.a, x.b, None
+        if Vd:
+            ad, bd, vm, x = make_xvocab(x, Vd, 0.8, seed=k)
+        args = [to_device(v) for v in (x.t, ad, bd, x.draft_tokens, x.draft_probs, x.uniforms, x.temperature)]
+        calls.append((x, args, None if vm is None else to_device(vm), full))
+    for turn in range(3):
+        for k, (x, args, vm, full) in enumerate(calls):
+            out = asp.fuse_verify(*args, return_gate=True, return_full=full, vocab_map=vm, workspace=ws)
+            torch.cuda.synchronize()
+            g = [v.cpu().numpy() for v in out]
+            assert (g[0] >= 0).all() and ws.timeouts() == 0
+            _note(compare(x, g, label=f"one workspace, turn {turn} call {k}"))
+            if full:
+                compare_full(x, g[4], label=f"one workspace, turn {turn} call {k}")
 
 
 # ----------------------------------------------------------- early exit --
