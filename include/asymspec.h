@@ -169,8 +169,10 @@ int asymspec_workspace_clear(void* workspace, size_t workspace_bytes, void* stre
  *                       the workgroups that read the logits, from registers
  *                       (4 (K+1) V bytes per request), or, with the KL gate and
  *                       for cross-family calls, by a second kernel on `stream`
- *                       that reads them again; one workgroup per 32 KiB chunk
- *                       of a row, so B (K+1) times the chunks per row must stay
+ *                       that reads them again (as do rows whose workgroups
+ *                       could not wait for each other, for instance beside a
+ *                       call on another stream); one workgroup per 32 KiB
+ *                       chunk of a row, so B (K+1) times the chunks per row must stay
  *                       below 2^31 (else E_ARG)
  *   workspace           device scratch of >= asymspec_workspace_size bytes,
  *                       256-byte aligned, contents opaque between calls

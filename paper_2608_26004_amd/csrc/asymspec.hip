@@ -11,8 +11,9 @@
 // The launch is an ordered list of work items (schedule.h), one workgroup per
 // item, so the hardware dispatcher hands them out in list order and balances
 // them over the compute units.  Statistics items (stats.h) stream every logit
-// once from HBM and never wait; per request, a decide, S pass-2 and a pick
-// item (resolve.h) follow a few requests behind and re-read only the rows
+// once from HBM and never wait (with full rows, they wait a bounded time for
+// the other items of their row: full.h); per request, a decide, S pass-2 and a
+// pick item (resolve.h) follow a few requests behind and re-read only the rows
 // whose outcome needs a second pass.
 //
 // Cross-workgroup records are arrays of 64-bit slots whose high word is the
@@ -76,8 +77,9 @@ static bool make_layout(int B, int K, int V, int dtype, Layout& L, int Vd = 0) {
   L.S = (int)S;
   L.rows = (size_t)B * (K + 1);
   size_t off = 0;
-  // the timeout counter first, at a place that does not depend on the shape
-  L.off_err = off;  off = align_up(off + 8, 256);
+  // the timeout counter first, at a place that does not depend on the shape,
+  // and the late-full-rows slot beside it
+  L.off_err = off;  off = align_up(off + 16, 256);
   L.off_rec1 = off; off = align_up(off + L.rows * L.S * kR1 * 8, 256);
   L.off_dec = off;  off = align_up(off + (size_t)B * (kDecHdr + (size_t)(K + 1) * kDecRow) * 8, 256);
   L.off_rec2 = L.off_xv = off;
@@ -143,6 +145,15 @@ static const void* dump_ptr_dt(int dm) {
   if (dm == kDeltaA) return (const void*)dump_kernel<DT, kDeltaA>;
   if (dm == kDeltaTB) return (const void*)dump_kernel<DT, kDeltaTB>;
   return (const void*)dump_kernel<DT, kDeltaAB>;
+}
+template <int DT>
+static const void* full_rest_ptr_dt(int dm) {
+  if (dm == kDeltaA) return (const void*)full_rest_kernel<DT, kDeltaA>;
+  if (dm == kDeltaTB) return (const void*)full_rest_kernel<DT, kDeltaTB>;
+  return (const void*)full_rest_kernel<DT, kDeltaAB>;
+}
+static const void* full_rest_ptr(int dtype, int dm) {
+  return dtype == ASYMSPEC_BF16 ? full_rest_ptr_dt<ASYMSPEC_BF16>(dm) : full_rest_ptr_dt<ASYMSPEC_FP32>(dm);
 }
 static const void* dump_ptr(int dtype, int dm) {
   return dtype == ASYMSPEC_BF16 ? dump_ptr_dt<ASYMSPEC_BF16>(dm) : dump_ptr_dt<ASYMSPEC_FP32>(dm);
@@ -304,6 +315,7 @@ static int fuse_verify_impl(const void* t, const void* a, const void* b, int dty
   A.dec = (uint64_t*)(ws + L.off_dec);
   A.rec2 = (uint64_t*)(ws + L.off_rec2);
   A.err = (uint32_t*)(ws + L.off_err);
+  A.full_late = (uint64_t*)(ws + L.off_err + 8);
   A.stream_bytes = (unsigned long long)B * (K + 1) * (unsigned long long)V * (dtype == ASYMSPEC_BF16 ? 2ull : 4ull);
   A.B = B; A.K = K; A.V = V; A.S = L.S;
   A.beta = params->beta; A.gamma = params->gamma; A.gate_mode = params->gate_mode;
@@ -323,7 +335,8 @@ static int fuse_verify_impl(const void* t, const void* a, const void* b, int dty
   // lags scale with the number of workgroups the chip holds at once
   const int ee_rows = ee ? (params->early_rows > 0 ? params->early_rows : 2) : 0;
   // the full rows are written by the statistics items, or by a second kernel
-  // (a row's items wait for each other: its share of an XCD must fit there)
+  // (a row's items wait for each other: its share of an XCD must fit there, or
+  // they would mostly run late)
   const bool kl = params->gate_mode == ASYMSPEC_GATE_KL;
   const bool in_stats = fused_logprobs_full != nullptr && vmap == nullptr && !kl &&
                         (L.S + 7) / 8 + 1 <= di->max_blocks_full[dtype] / 8;
@@ -363,8 +376,9 @@ static int fuse_verify_impl(const void* t, const void* a, const void* b, int dty
     e = hipLaunchKernel(kernel_ptr(dtype, var, params->delta_mode), dim3(grid), dim3(kThreads), args, 0,
                         (hipStream_t)stream);
     if (e == hipSuccess && in_stats) {
-      hipLaunchKernelGGL(full_check_kernel, dim3((B + 255) / 256), dim3(256), 0, (hipStream_t)stream, A);
-      e = hipGetLastError();
+      e = hipLaunchKernel(full_rest_ptr(dtype, params->delta_mode),
+                          dim3((unsigned)std::min<unsigned long long>(nblk, 2ull * di->n_cu)), dim3(kThreads), args, 0,
+                          (hipStream_t)stream);
     }
   }
   if (e == hipSuccess && fused_logprobs_full != nullptr && !in_stats) {

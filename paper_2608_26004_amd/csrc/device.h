@@ -82,7 +82,8 @@ enum { R1_R = 0, R1_S = kSlots, R1_ARG = 2 * kSlots, R1_NEQ = 2 * kSlots + 1, R1
 // by the decide item; pass-2 and pick items load it into LDS (Smem::req,
 // Smem::rows).
 enum { H_STATE = 0, H_J = 1, H_TASK_LO = 2, H_TASK_HI = 3, H_SAMP = 4, H_USED = 5, H_VERDICT = 5, H_FULL = 6, kDecHdr = 8 };
-// H_FULL: set when the request's full rows could not be completed.
+// H_FULL: set when an item of the request left its part of the full rows to the
+// kernel behind this one (full_norm).
 // Early exit: the verdict on a request's first rows (a sure rejection among
 // them makes the other rows unneeded).
 enum { kVerdictRead = 1, kVerdictSkip = 2 };
@@ -127,6 +128,7 @@ struct KArgs {
   float* full;        // full log-probability rows written by the statistics items
   uint64_t* rec1; uint64_t* dec; uint64_t* rec2;
   uint32_t* err;
+  uint64_t* full_late;   // slot: some item of this call left full rows unwritten
   unsigned long long stream_bytes;   // bytes of each logit array
   int B, K, V, S;
   int P2;             // pass-2 items per chunk

@@ -35,11 +35,25 @@ __global__ __launch_bounds__(kThreads) void dump_kernel(KArgs A, float* out) {
   full_chunk<DT, DM>(A, out, row_span<DT>(A, row), m, fused, nb, c, l2);
 }
 
-// Requests whose full rows could not be completed (a wait between the items of
-// a row timed out) are marked invalid.
-__global__ void full_check_kernel(KArgs A) {
-  const int req = (int)(blockIdx.x * blockDim.x + threadIdx.x);
-  if (req < A.B && tag_ok(ld_tag(dec_hdr(A, req) + H_FULL), A.epoch)) A.acc_out[req] = -1;
+// Behind a decision kernel whose statistics items write the full rows: the rows
+// of the requests that some item left (H_FULL), all of them, read again.  A fixed
+// grid that ends at one word when nothing is left, as in nearly every call.
+template <int DT, int DM>
+__global__ __launch_bounds__(kThreads) void full_rest_kernel(KArgs A) {
+  if (!tag_ok(*A.full_late, A.epoch)) return;
+  const int S = A.S, nrow = A.K + 1;
+  const long long nblk = (long long)A.B * nrow * S;
+  for (long long b = blockIdx.x; b < nblk; b += gridDim.x) {
+    const int row = (int)(b / S), m = (int)(b - (long long)row * S);
+    const int req = row / nrow, i = row - req * nrow;
+    const uint64_t* hdr = dec_hdr(A, req);
+    // (a request whose decision failed is marked invalid and has no normalisers)
+    if (!tag_ok(hdr[H_FULL], A.epoch) || !tag_ok(hdr[H_STATE], A.epoch) || pay(hdr[H_STATE]) == kStateFailed) continue;
+    const uint64_t* blk = dec_row(A, req, i);
+    const bool fused = i < A.K || A.fuse_bonus != 0;
+    full_chunk<DT, DM>(A, A.full, row_span<DT>(A, row), m, fused, (pay(blk[D_STATUS]) & kStNeq) != 0u,
+                       (double)payf(blk[D_C]), payd(blk[D_L2E_LO], blk[D_L2E_HI]));
+  }
 }
 
 }  // namespace asym

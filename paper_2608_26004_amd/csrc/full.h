@@ -56,15 +56,48 @@ DEV void full_store(const KArgs& A, const RowGeo& g, int rel, const float* x, do
   full_put<DT>(A, A.full, g, rel, x, c, l2);
 }
 
+// Bound of an item's wait for the other items of its row, in ticks of the 100 MHz
+// clock (0.5 ms; a whole call of B = 128, K = 6, V = 151936 takes 0.28): an item
+// that runs late only costs a second read of its request.
+constexpr uint64_t kFullTicks = 50000;
+// Polls of one lane within that bound; over at once when another item of the
+// call has already run late.
+struct FullPoll {
+  uint64_t t0;
+  int n;
+  DEV FullPoll() : t0(__builtin_amdgcn_s_memrealtime()), n(0) {}
+  DEV bool again(const KArgs& A) {
+    const int reps = 1 << (n < kPollMaxShift ? n : kPollMaxShift);
+    for (int i = 0; i < reps; ++i) __builtin_amdgcn_s_sleep(2);
+    ++n;
+    if (tag_ok(ld_tag(A.full_late), A.epoch)) return false;
+    const uint64_t most = A.poll_ticks < kFullTicks ? A.poll_ticks : kFullTicks;
+    return __builtin_amdgcn_s_memrealtime() - t0 <= most;
+  }
+};
+// The fp32 value in the tagged slot at p; ok is cleared when it came too late.
+DEV float full_wait(const uint64_t* p, const KArgs& A, FullPoll& pl, bool& ok) {
+  uint64_t v = ld_tag(p);
+  while (ok && !tag_ok(v, A.epoch)) {
+    ok = pl.again(A);
+    v = ld_tag(p);
+  }
+  return payf(v);
+}
+
 // The log2 normaliser of row g's emission distribution (slot `slot`) from the
-// records of all its chunks: wave 0 waits for them (bounded).  False, in every
-// thread, when a wait timed out: the request is then marked (H_FULL) and its
-// accept_len set to -1 after the kernel.
+// records of all its chunks: wave 0 waits for them.  False, in every thread,
+// when they came too late: the chunk is then left to full_rest_kernel, which
+// runs behind this kernel and writes the marked requests' rows (H_FULL).
 //
-// The items of a row wait for each other.  They are neighbours in the list, each
-// XCD starts its share of the workgroups in list order and holds more of them
-// (at least 64) than the at most 33 that a row of up to 256 chunks puts there, so the
-// items of the oldest unfinished row are always started.
+// The items of a row wait for each other, also for later ones.  They are
+// neighbours in the list, each XCD starts its share of the workgroups in list
+// order and holds more of them (at least 64) than the at most 33 that a row of up
+// to 256 chunks puts there, so in a launch that has the chip to itself the items
+// of the oldest unfinished row are always started.  Beside another launch they
+// need not be: two calls on two streams can each hold the slots that the other's
+// oldest row needs.  So the wait is short, counts as no error, and the first item
+// to run late stops every other one of its call from waiting.
 template <int SLOT>
 DEV bool full_norm(const KArgs& A, const RowGeo& g, Smem& sm, double& l2) {
   const int lane = lane_id();
@@ -73,19 +106,23 @@ DEV bool full_norm(const KArgs& A, const RowGeo& g, Smem& sm, double& l2) {
     float R = kFloorM;
     double sum = 0.0;
     bool ok = true;
+    FullPoll pl;
     // first every record's reference, then the sums against the largest
-    for (int ch = lane; ch < A.S; ch += 64) R = fmaxf(R, wait_f32(base + (size_t)ch * kR1 + R1_R + SLOT, A, ok));
+    for (int ch = lane; ch < A.S; ch += 64) R = fmaxf(R, full_wait(base + (size_t)ch * kR1 + R1_R + SLOT, A, pl, ok));
     R = wave_max(R);
     for (int ch = lane; ch < A.S; ch += 64) {
       const float r = payf(ld_tag(base + (size_t)ch * kR1 + R1_R + SLOT));
-      sum += (double)(wait_f32(base + (size_t)ch * kR1 + R1_S + SLOT, A, ok) * __builtin_amdgcn_exp2f(r - R));
+      sum += (double)(full_wait(base + (size_t)ch * kR1 + R1_S + SLOT, A, pl, ok) * __builtin_amdgcn_exp2f(r - R));
     }
     sum = wave_sum_d(sum);
     const bool in = __all(ok);
     if (lane == 0) {
       sm.dd[0] = (double)R + log2_dbl(sum);
       sm.flags[0] = in ? 1 : 0;
-      if (!in) st_tag(dec_hdr(A, g.req) + H_FULL, 1u, A.epoch);
+      if (!in) {
+        st_tag(dec_hdr(A, g.req) + H_FULL, 1u, A.epoch);
+        st_tag(A.full_late, 1u, A.epoch);
+      }
     }
   }
   __syncthreads();

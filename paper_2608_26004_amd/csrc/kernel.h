@@ -46,11 +46,14 @@ DEV void stats_dispatch(const KArgs& A, int req, int sub, Smem& sm) {
 #endif
 
 // One workgroup per item.  An item waits only for items earlier in the list
-// (lower workgroup index), and each XCD starts its share of the workgroups in
+// (lower workgroup index; the kFull instances excepted), and each XCD starts its share of the workgroups in
 // index order, so the lowest waiting workgroup always waits on items that are
 // running or queued behind workgroups that never wait: the list drains
 // whether or not every workgroup fits on the chip at once.  The waits are
-// bounded besides (Poll), and a timeout is counted in the workspace.
+// bounded besides (Poll), and a timeout is counted in the workspace.  A
+// statistics item of a kFull instance also waits for the later items of its row,
+// within a short bound of its own; when that runs out it leaves its rows to the
+// kernel behind this one and ends, so these launches drain as well (full.h).
 // kKL: calls with the KL gate, whose draft rows also sum the divergence
 // beside the A slot (a kernel of its own, so that the extra registers of
 // those items do not weigh on the other gates' kernels).

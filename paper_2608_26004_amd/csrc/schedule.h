@@ -18,7 +18,9 @@
 //   * the pick item of request q - L3         (1 item),
 // each present only when its request index lies in [0, B).  Without early
 // exit G = K + 1 and Lv = Ls = 0.  An item only ever waits for items earlier
-// in the list, so the lowest unfinished item can always proceed.  The lags
+// in the list, so the lowest unfinished item can always proceed (statistics
+// items that write full rows also wait for later items of their row, for a short
+// time, and end without them: full.h).  The lags
 // keep those waits rare: each spans a multiple of the number of items in
 // flight at once.
 //

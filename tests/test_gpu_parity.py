@@ -406,7 +406,7 @@ def test_full_logprobs_chunks(gpu, dtype, V, K):
 
 
 def test_full_logprobs_timed_out_rows_are_marked(gpu):
-    """A wait bound of 20 ns: a request whose rows could not all be written
+    """A wait bound of 20 ns: a request whose decision could not be completed
     has accept_len = -1; the full rows of the others are the oracle's."""
     import paper_2608_26004_amd as asp
     import torch
@@ -426,6 +426,94 @@ def test_full_logprobs_timed_out_rows_are_marked(gpu):
     assert ws.timeouts() > 0 and len(good) < x.B
     if len(good):
         compare_full(x, full.cpu().numpy(), requests=good.tolist(), label="full rows beside timed-out ones")
+
+
+def _full_rows_inputs(B, K, V, seed, dtype=None):
+    """Random full-row inputs on the GPU, and the rows' log-softmax in fp64 of
+    the fp32 fused logits, on a list of requests."""
+    import torch
+    dev = torch.device("cuda")
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(seed)
+    t, a, b = (3.0 * torch.randn(B, K + 1, V, device=dev, generator=gen).to(dtype or torch.bfloat16)
+               for _ in range(3))
+    d = torch.randint(0, V, (B, K), dtype=torch.int32, device=dev, generator=gen)
+    q = torch.full((B, K), 0.5, device=dev)
+    u = torch.rand(B, K + 1, device=dev, generator=gen)
+    tau = torch.where(torch.arange(B, device=dev) % 2 == 0, 0.8, 0.0)
+
+    def rows(reqs):
+        f = t[reqs].float() + (a[reqs].float() - b[reqs].float())
+        f[:, K] = t[reqs, K].float()
+        th = torch.where(tau[reqs] > 0, tau[reqs], 1.0).double()
+        return (f.double() / th[:, None, None]).log_softmax(-1)
+
+    return (t, a, b, d, q, u, tau), rows
+
+
+@pytest.mark.parametrize("delta", [0, 2])
+def test_full_rows_left_by_late_items_are_written(gpu, delta):
+    """A wait bound of 20 ns, and so long a list that the early requests'
+    decisions find everything in at first sight: nearly every item runs late
+    for its row, and the requests whose decision was completed still get their
+    full rows, from the kernel behind, and are not marked."""
+    import paper_2608_26004_amd as asp
+    import torch
+    args, rows = _full_rows_inputs(2000, 1, 50000, 3)
+    t, a, b = args[:3]
+    if delta == 2:
+        args = (t, b, a) + args[3:]     # delta = t - b, checked through its own formula below
+    ws = asp.Workspace(t.device)
+    B, K, V = 2000, 1, 50000
+    out = [torch.full((B,), -7, dtype=torch.int32, device=t.device) for _ in range(2)]
+    out += [torch.zeros(B, K + 1, device=t.device), None, torch.full((B, K + 1, V), float("nan"), device=t.device)]
+    try:
+        asp.set_wait_limit(2)
+        asp.fuse_verify(*args, workspace=ws, out=out, delta_mode=delta)
+        torch.cuda.synchronize()
+    finally:
+        asp.set_wait_limit(0)
+    good = torch.nonzero(out[0] >= 0).flatten()
+    print(f"[full] wait bound 20 ns: {len(good)} of {B} requests decided")
+    assert len(good) >= 200 and ws.timeouts() > 0
+    sel = good[::max(1, len(good) // 100)]
+    if delta == 0:
+        ref = rows(sel)
+    else:
+        f = t[sel].float() + (t[sel].float() - a[sel].float())      # a is passed as b
+        f[:, K] = t[sel, K].float()
+        th = torch.where(args[6][sel] > 0, args[6][sel], 1.0).double()
+        ref = (f.double() / th[:, None, None]).log_softmax(-1)
+    err = (out[4][sel].double() - ref).abs().max().item()
+    assert err <= 1e-5, err
+
+
+def test_full_rows_on_two_streams(gpu):
+    """Full-row calls on two streams at once, a workspace each: the same
+    decisions and rows as one after the other."""
+    import paper_2608_26004_amd as asp
+    import torch
+    sets = [_full_rows_inputs(64, 2, 151936, 5), _full_rows_inputs(40, 1, 600001, 6)]
+    alone = [asp.fuse_verify(*s[0], return_full=True, workspace=asp.Workspace(s[0][0].device)) for s in sets]
+    torch.cuda.synchronize()
+    for k, (args, rows) in enumerate(sets):
+        sel = torch.tensor([0, 1, args[0].shape[0] - 1], device=args[0].device)
+        assert (alone[k][3][sel].double() - rows(sel)).abs().max().item() <= 1e-5
+    streams = [torch.cuda.Stream() for _ in sets]
+    wss = [asp.Workspace(torch.device("cuda")) for _ in sets]
+    for turn in range(8):
+        outs = []
+        for (args, _), st, ws in zip(sets, streams, wss):
+            st.wait_stream(torch.cuda.current_stream())
+            with torch.cuda.stream(st):
+                outs.append(asp.fuse_verify(*args, return_full=True, workspace=ws))
+        for st in streams:
+            torch.cuda.current_stream().wait_stream(st)
+        torch.cuda.synchronize()
+        for got, ref, ws in zip(outs, alone, wss):
+            assert ws.timeouts() == 0
+            assert torch.equal(got[0], ref[0]) and torch.equal(got[1], ref[1])
+            assert (got[3] - ref[3]).abs().max().item() <= 1e-5
 
 
 # ------------------------------------------- cross-family vocabularies --
