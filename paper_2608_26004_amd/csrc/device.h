@@ -98,9 +98,9 @@ enum {
   D_RF,         // reference exponent of p~ (drafts) or of the bonus weights
   D_ISF,        // 1 / sum of p~ weights (drafts)
   D_RQ, D_ISQ,  // the same for the proposal q = softmax(a / tau)
-  D_JLA, D_JLB, D_JSA, D_JSB,   // JSD terms (JsdConst)
+  D_JRA, D_JRB, D_JKA, D_JKB, D_JSA, D_JSB,   // JSD terms (JsdConst)
   D_LPD,        // log p~(d): fused log-probability of the draft token
-  D_STATUS,     // kStDecided | kStAccept | kStDraft | kStNeq
+  D_STATUS,     // kStDecided | kStAccept | kStDraft | kStNeq | kStWide
   D_THR_LO, D_THR_HI,   // open rows: accepted iff D > thr (fp64)
   D_L2E_LO, D_L2E_HI,   // log2 normaliser (fp64) of the emission distribution
   D_ARG,        // greedy: argmax of f (drafts) or t (bonus)
@@ -110,8 +110,9 @@ enum {
   kDecRow = 24
 };
 enum { kTaskJsd = 1, kTaskRes = 2, kTaskBonus = 4 };
-// kStSkip: a row after a sure rejection that early exit did not read.
-enum { kStDecided = 1, kStAccept = 2, kStDraft = 4, kStNeq = 8, kStSkip = 16 };
+// kStSkip: a row after a sure rejection that early exit did not read.  kStWide:
+// the row's log-normalisers need two words in its JSD terms (JsdConst).
+enum { kStDecided = 1, kStAccept = 2, kStDraft = 4, kStNeq = 8, kStSkip = 16, kStWide = 32 };
 
 // Pass 2 splits each chunk into P2 in {1, 2, 4, 8} contiguous parts, one
 // item each.  Pass-2 record of one (request, row, chunk): the JSD partial of each
@@ -675,35 +676,55 @@ DEV float bonus_elem(float t, float c, float Rt) {
   return __builtin_amdgcn_exp2f(__builtin_fmaf(t, c, -Rt));
 }
 // JSD term P log2(2P/(P+Q)) + Q log2(2Q/(P+Q)), P = softmax(a), Q = softmax(b)
-// (Eq. 3), its two halves summed apart.  log2 P = a log2 e - LA uses La =
-// fl(LA): the rounding LA - La changes the logarithms of P and P + Q such that it
-// cancels from the sum of the terms to first order, and scales P, which sa
-// takes back from the half's sum (sb likewise).  10 plain and 3 transcendental
-// operations a pair; with LA in two words they were 16 and 3 (B = 128, K = 6, V =
-// 151936 with the gate output, bound by these operations: 206 -> 196 us; error
-// of D and the threshold against 64 bits 3.3e-7 either way).  log2 of (P + Q) / 2
-// in place of 1 - log2(P + Q) was 3.7e-7.  Logarithms are raised to -100 (a
-// token a view masks would give 0 * inf); such a P counts for nothing.
-struct JsdConst { float La, Lb, sa, sb; };
-DEV JsdConst jsd_make(double LA, double LB) {
-  const float La = (float)LA, Lb = (float)LB;
-  return JsdConst{La, Lb, (float)(1.0 + ((double)La - LA) * kLn2), (float)(1.0 + ((double)Lb - LB) * kLn2)};
+// (Eq. 3), its two halves summed apart.  log2 P = a log2 e - LA, LA = R + k + e
+// with fp32 words R and k: the rest e changes the logarithms of P and P + Q such
+// that it cancels from the sum of the terms to first order, and scales P, which sa
+// takes back from the half's sum (sb likewise).  A row whose normalisers are below
+// kJsdNarrow needs one word (R = fl(LA), k = 0, e at most 2^-15, a second-order
+// error below 3e-10): 10 plain and 3 transcendental operations a pair, against
+// 16 and 3 with LA in a reference and two words (B = 128, K = 6, V = 151936 with
+// the gate output, bound by these operations: 206 -> 196 us; error of D and the
+// threshold against 64 bits 3.3e-7 either way).  fl(LA) is worse the further the
+// logits lie from 0 (D 4.6e-6 off at 1e5, 2.9e-7 with two words), so other rows are wide: R is the sums'
+// reference exponent, k the logarithm of the sum, two operations more.  log2 of
+// (P + Q) / 2 in place of 1 - log2(P + Q) was 3.7e-7.  Logarithms are raised to
+// -100 (a token a view masks would give 0 * inf); such a P counts for nothing.
+constexpr double kJsdNarrow = 1024.0;
+struct JsdConst { float Ra, Rb, ka, kb, sa, sb; };
+// RA, RB: reference exponents; lA, lB: logarithms of the sums relative to them.
+DEV JsdConst jsd_make(float RA, double lA, float RB, double lB, bool& wide) {
+  const double LA = (double)RA + lA, LB = (double)RB + lB;
+  wide = !(fabs(LA) < kJsdNarrow && fabs(LB) < kJsdNarrow);
+  JsdConst k;
+  k.Ra = wide ? RA : (float)LA;
+  k.Rb = wide ? RB : (float)LB;
+  k.ka = wide ? (float)lA : 0.0f;
+  k.kb = wide ? (float)lB : 0.0f;
+  // (the differences of nearby values are exact)
+  const double ea = wide ? (double)k.ka - lA : (double)k.Ra - LA;
+  const double eb = wide ? (double)k.kb - lB : (double)k.Rb - LB;
+  k.sa = (float)(1.0 + ea * kLn2);
+  k.sb = (float)(1.0 + eb * kLn2);
+  return k;
 }
 struct JsdAcc { float p, q; };
+// kWide: rows of either sort (k = 0 changes nothing on a narrow one).
+template <bool kWide>
 DEV void jsd_add(JsdAcc& acc, float a, float b, const JsdConst& k) {
-  const float lp = fmaxf(__builtin_fmaf(a, kL2E, -k.La), -100.0f);
-  const float lq = fmaxf(__builtin_fmaf(b, kL2E, -k.Lb), -100.0f);
+  const float xa = __builtin_fmaf(a, kL2E, -k.Ra), xb = __builtin_fmaf(b, kL2E, -k.Rb);
+  const float lp = fmaxf(kWide ? xa - k.ka : xa, -100.0f);
+  const float lq = fmaxf(kWide ? xb - k.kb : xb, -100.0f);
   const float P = __builtin_amdgcn_exp2f(lp), Q = __builtin_amdgcn_exp2f(lq);
   const float l1 = 1.0f - __builtin_amdgcn_logf(P + Q);
   acc.p = __builtin_fmaf(P, lp + l1, acc.p);
   acc.q = __builtin_fmaf(Q, lq + l1, acc.q);
 }
 // The terms of one vector of each view, summed on their own first.
-template <int VE, class EA, class EB>
+template <int VE, bool kWide, class EA, class EB>
 DEV void jsd_vec(JsdAcc& acc, const JsdConst& k, EA&& xa, EB&& xb) {
   JsdAcc v{0.0f, 0.0f};
   #pragma unroll
-  for (int e = 0; e < VE; ++e) jsd_add(v, xa(e), xb(e), k);
+  for (int e = 0; e < VE; ++e) jsd_add<kWide>(v, xa(e), xb(e), k);
   acc.p += v.p;
   acc.q += v.q;
 }

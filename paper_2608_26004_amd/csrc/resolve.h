@@ -34,8 +34,8 @@ DEV ResidConst resid_const(const KArgs& A, const uint32_t* cst) {
                     __uint_as_float(cst[D_ISF]), __uint_as_float(cst[D_RQ]), __uint_as_float(cst[D_ISQ])};
 }
 DEV JsdConst jsd_const(const uint32_t* cst) {
-  return JsdConst{__uint_as_float(cst[D_JLA]), __uint_as_float(cst[D_JLB]), __uint_as_float(cst[D_JSA]),
-                  __uint_as_float(cst[D_JSB])};
+  return JsdConst{__uint_as_float(cst[D_JRA]), __uint_as_float(cst[D_JRB]), __uint_as_float(cst[D_JKA]),
+                  __uint_as_float(cst[D_JKB]), __uint_as_float(cst[D_JSA]), __uint_as_float(cst[D_JSB])};
 }
 
 // ------------------------------------------------------------------ decide
@@ -50,19 +50,25 @@ DEV void classify_row(const KArgs& A, const RowGeo& g, const Gather& gq, float M
   const int kind = g.kind;
   const bool draft = kind_draft(kind);
   const bool samp = kind_samp(kind);
-  double L2[kSlots];
+  double lg[kSlots], L2[kSlots];
   #pragma unroll
-  for (int s = 0; s < kSlots; ++s) L2[s] = (double)R[s] + log2_dbl(Sp[s]);
+  for (int s = 0; s < kSlots; ++s) {
+    lg[s] = log2_dbl(Sp[s]);
+    L2[s] = (double)R[s] + lg[s];
+  }
   const int gm = A.gate_mode;
   #pragma unroll
   for (int i = 0; i < kDecRow; ++i) v[i] = 0u;
   int decided = 1, accept = 0;
+  bool wide = false;
   double thr = 0.0;
   v[D_C] = __float_as_uint(g.c);
   if (draft) {
-    const JsdConst jk = jsd_make(L2[sA], L2[sB]);
-    v[D_JLA] = __float_as_uint(jk.La);
-    v[D_JLB] = __float_as_uint(jk.Lb);
+    const JsdConst jk = jsd_make(R[sA], lg[sA], R[sB], lg[sB], wide);
+    v[D_JRA] = __float_as_uint(jk.Ra);
+    v[D_JRB] = __float_as_uint(jk.Rb);
+    v[D_JKA] = __float_as_uint(jk.ka);
+    v[D_JKB] = __float_as_uint(jk.kb);
     v[D_JSA] = __float_as_uint(jk.sa);
     v[D_JSB] = __float_as_uint(jk.sb);
     const float fd = fuse_masked(gq.t, gq.a, gq.b, A.beta, A.delta_mode);
@@ -165,7 +171,7 @@ DEV void classify_row(const KArgs& A, const RowGeo& g, const Gather& gq, float M
   v[D_THR_LO] = dlo(thr);
   v[D_THR_HI] = dhi(thr);
   v[D_STATUS] = (decided ? kStDecided : 0) | (accept ? kStAccept : 0) | (draft ? kStDraft : 0) |
-                (neq ? kStNeq : 0);
+                (neq ? kStNeq : 0) | (wide ? kStWide : 0);
 }
 
 // The decision of request req (Alg. 1, Eq. 2-4) from the statistics records
@@ -546,7 +552,7 @@ DEV void pass2_sums(const KArgs& A, const RowGeo& g, long long rel0, int nk, boo
       // each task's element terms under its own (uniform) branch, so that a
       // row without a task never evaluates that task's terms
       if (dj)
-        jsd_vec<VE>(accj, jk, [&](int e) { return Elem<DT>::get(va[k], e); },
+        jsd_vec<VE, true>(accj, jk, [&](int e) { return Elem<DT>::get(va[k], e); },
                     [&](int e) { return Elem<DT>::get(vb[k], e); });
       if (dr || db) {
         float vr[VE];
@@ -586,7 +592,8 @@ DEV void pass2_sums_any(const KArgs& A, const RowGeo& g, long long rel0, int nk,
     pass2_sums<DT, 1, DM, kNb, false, kGF>(A, g, rel0, nk, dj, dr, db, rk, jk, accj, seg);
 }
 
-// The divergence of the rows in jm, which have no other task: their vectors
+// The divergence of the rows in jm, which have no other task and are not wide
+// (JsdConst): their vectors
 // form one sequence, row after row, and the next group of a and b is in flight
 // while the current one is reduced; a row's partial costs one wave reduction
 // and all rows share one barrier.  kG vectors per group.  (One row after another
@@ -633,7 +640,7 @@ DEV void pass2_jsd(const KArgs& A, int req, int m, int part, int nk, unsigned lo
     const JsdConst jk = jsd_const(sm.rows[i]);
     #pragma unroll
     for (int k = 0; k < kG; ++k)
-      jsd_vec<VE>(acc, jk, [&](int e) { return Elem<DT>::get(va[k], e); },
+      jsd_vec<VE, false>(acc, jk, [&](int e) { return Elem<DT>::get(va[k], e); },
                   [&](int e) { return Elem<DT>::get(vb[k], e); });
     if (last) {
       const float wj = wave_sum(jsd_sum(acc, jk));
@@ -671,8 +678,9 @@ DEV void pass2_item(const KArgs& A, int req, int sub, Smem& sm) {
   unsigned long long tmask = (unsigned long long)sm.req[R_TASK_LO] | ((unsigned long long)sm.req[R_TASK_HI] << 32);
   // only rows 0..K of the request (K + 1 <= 64)
   if (A.K + 1 < 64) tmask &= (1ull << (A.K + 1)) - 1ull;
-  // the rows whose only task is their divergence
-  const unsigned long long jm = __ballot(lane <= A.K && sm.rows[lane][D_TASK] == (uint32_t)kTaskJsd) & tmask;
+  // the rows whose only task is their divergence, in its one-word form
+  const unsigned long long jm = __ballot(lane <= A.K && sm.rows[lane][D_TASK] == (uint32_t)kTaskJsd &&
+                                         (sm.rows[lane][D_STATUS] & kStWide) == 0u) & tmask;
   if (jm != 0) {
     if (nk >= 4) pass2_jsd<DT, 4>(A, req, m, part, nk, jm, sm);
     else if (nk >= 2) pass2_jsd<DT, 2>(A, req, m, part, nk, jm, sm);

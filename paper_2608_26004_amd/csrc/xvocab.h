@@ -628,7 +628,7 @@ void xv_pass2_kernel(KArgs A, XArgs X) {
         if (p0 + k * 64 >= pe) break;
         const float xa = XT::a(pr[k]), xb = XT::b(pr[k]);
         // (masked: no mass in either view)
-        if (dj) jsd_add(accj, in ? xa : -INFINITY, in ? xb : -INFINITY, jk);
+        if (dj) jsd_add<true>(accj, in ? xa : -INFINITY, in ? xb : -INFINITY, jk);
         if (dr || db) {
           float v = dr ? resid_elem<DM>(xt[k], xa, xb, rk) : bonus_elem(xt[k], rk.c, rk.Rf);
           v = in ? v : 0.0f;

@@ -78,6 +78,32 @@ def test_divergence_rows(gpu, dtype, B, K, V):
         _note(compare(x, g, gate_mode=mode, label=f"divergence rows {dtype} B={B} K={K} V={V} mode={mode}"))
 
 
+@pytest.mark.parametrize("B,tau,Vd", [(3, 0.0, 0), (3, 0.9, 0), (90, 0.0, 0), (3, 0.9, 30000)])
+def test_divergence_of_logits_far_from_zero(gpu, B, tau, Vd):
+    """Drafter logits moved by 2^20: a shift that fp32 takes exactly (the logits
+    are multiples of 1/8) and that changes no softmax, so D stays what it was.
+    The log-normalisers' rounding at 1.5e6 is 0.06; in one fp32 word it was
+    1e-4 of D.  Bound: D is 3e-7 off 64 bits at either place, so 1e-6."""
+    x = synth.generate(B=B, K=3, V=40001, dtype="fp32", rho=1.0, tau=tau, seed=20 + B)
+    x.t, x.a, x.b = (np.round(v * 8).astype(np.float32) / 8 for v in (x.t, x.a, x.b))
+    vocab = lambda y: None      # noqa: E731
+    if Vd:
+        from parity_util import make_xvocab
+        ad, bd, vm, x = make_xvocab(x, Vd, 0.6, seed=9)
+        ad, bd = (np.round(v * 8).astype(np.float32) / 8 for v in (ad, bd))
+        vocab = lambda off: (ad + np.float32(off), bd + np.float32(off), vm)    # noqa: E731
+    near = run_gpu(x, vocab=vocab(0.0))
+    _note(compare(x, near, label=f"divergence at 0 B={B} tau={tau} Vd={Vd}"))
+    x.a, x.b = x.a + np.float32(2 ** 20), x.b + np.float32(2 ** 20)
+    far = run_gpu(x, vocab=vocab(2.0 ** 20))
+    assert np.array_equal(far[0], near[0])
+    d0, d1 = near[3][..., 0].astype(np.float64), far[3][..., 0].astype(np.float64)
+    assert (d0 > 0.01).any()
+    err = np.abs(d1 - d0).max()
+    print(f"[divergence] B={B} tau={tau} Vd={Vd}: D moved by {err:.2e}")
+    assert err <= 1e-6, err
+
+
 def test_argmax_ties_across_waves_and_chunks(gpu):
     """Greedy rows whose fused maximum is attained twice, in the runs of two
     waves of one statistics item and in two chunks: the first index wins
