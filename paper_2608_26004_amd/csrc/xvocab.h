@@ -76,6 +76,7 @@ struct XArgs {
   int32_t* work;      // [1 + rows] number of rows with a pass-2 task, then those rows
   int T, U, nsub;
   int r0, r1;         // rows of each request this launch covers
+  unsigned b0;        // first of its blocks (a launch holds fewer than 2^32 threads)
 };
 
 // ------------------------------------------------------------------- lists
@@ -388,13 +389,12 @@ __global__ __launch_bounds__(XTile<DT>::kThr) __attribute__((amdgpu_waves_per_eu
 void xv_stats_kernel(KArgs A, XArgs X) {
   using XT = XTile<DT>;
   __shared__ XSmem<DT> sm;
-  // consecutive blocks go to the 8 XCDs in turn: the tiles of a row take
-  // blocks 8 apart, so they run on one XCD at about the same time
   const int lane = (int)threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   // consecutive blocks go to the 8 XCDs in turn: the tiles of a row take
   // blocks 8 apart, so they run on one XCD at about the same time
-  const int nr = X.r1 - X.r0, s = (int)blockIdx.x >> 3;
-  const int lr = s / X.T * 8 + ((int)blockIdx.x & 7), tile = s % X.T;
+  const unsigned blk = X.b0 + blockIdx.x;
+  const int nr = X.r1 - X.r0, s = (int)(blk >> 3);
+  const int lr = s / X.T * 8 + (int)(blk & 7u), tile = s % X.T;
   if (lr >= A.B * nr) return;
   XItem it = xv_item<DT>(A, X, lr / nr * (A.K + 1) + X.r0 + lr % nr, tile);
   if (X.r0 > 0) {

@@ -45,24 +45,30 @@ static hipError_t launch(KArgs A, const XLayout& L, char* base, int ee_rows, int
   A.sc.ee = (ee_rows >= 1 && ee_rows < nrow) ? 1 : 0;
   A.sc.G = A.sc.ee ? ee_rows : nrow;
   constexpr int kThr = XTile<DT>::kThr;
-  auto tiles = [&](int r0, int r1) {
+  // the statistics of rows [r0, r1) of every request: one workgroup per (row,
+  // tile), in launches of fewer than 2^32 threads, the most HIP takes (a multiple
+  // of 8 blocks each, so that a row's tiles stay on one XCD)
+  constexpr long long kMost = ((1LL << 32) / kThr - 1) / 8 * 8;
+  auto blocks = [&](int r0, int r1) { return ((long long)A.B * (r1 - r0) + 7) / 8 * 8 * X.T; };
+  auto stats = [&](int r0, int r1) {
     X.r0 = r0;
     X.r1 = r1;
-    return dim3((unsigned)(((long long)A.B * (r1 - r0) + 7) / 8 * 8 * X.T));
+    for (long long b0 = 0, n = blocks(r0, r1); b0 < n; b0 += kMost) {
+      X.b0 = (unsigned)b0;
+      hipLaunchKernelGGL((xv_stats_kernel<DT, DM>), dim3((unsigned)std::min(kMost, n - b0)), dim3(kThr), 0, st, A, X);
+    }
   };
   hipLaunchKernelGGL((xv_count_kernel<DT>), dim3(L.U), dim3(kThreads), 0, st, A, X);
   hipLaunchKernelGGL((xv_fill_kernel<DT>), dim3(L.U), dim3(kThreads), 0, st, A, X);
-  dim3 g = tiles(0, A.sc.G);
-  hipLaunchKernelGGL((xv_stats_kernel<DT, DM>), g, dim3(kThr), 0, st, A, X);
+  stats(0, A.sc.G);
   if (A.sc.ee) {
     hipLaunchKernelGGL((xv_decide_kernel<DT>), dim3(A.B), dim3(kThreads), 0, st, A, X, 1);
-    g = tiles(A.sc.G, nrow);
-    hipLaunchKernelGGL((xv_stats_kernel<DT, DM>), g, dim3(kThr), 0, st, A, X);
+    stats(A.sc.G, nrow);
   }
   hipLaunchKernelGGL((xv_decide_kernel<DT>), dim3(A.B), dim3(kThreads), 0, st, A, X, 0);
   // pass 2: what the chip holds at once (two workgroups per CU), a multiple of 8
-  g = dim3(std::min(tiles(0, nrow).x, (unsigned)std::max(8, 2 * n_cu / 8 * 8)));
-  hipLaunchKernelGGL((xv_pass2_kernel<DT, DM>), g, dim3(kThr), 0, st, A, X);
+  const long long g2 = std::min(blocks(0, nrow), (long long)std::max(8, 2 * n_cu / 8 * 8));
+  hipLaunchKernelGGL((xv_pass2_kernel<DT, DM>), dim3((unsigned)g2), dim3(kThr), 0, st, A, X);
   hipLaunchKernelGGL((xv_pick_kernel<DT, DM>), dim3(A.B), dim3(kThreads), 0, st, A, X);
   return hipGetLastError();
 }

@@ -697,6 +697,27 @@ def test_one_workspace_for_calls_of_every_kind(gpu):
                 compare_full(x, g[4], label=f"one workspace, turn {turn} call {k}")
 
 
+def test_xvocab_more_tiles_than_one_launch_holds(gpu):
+    """131073 requests of 64 rows, a tile each: 2^23 + 64 workgroups of 512
+    threads, where one launch takes fewer than 2^32 threads; 61 requests over
+    and over, each time the outputs of those 61 alone (which are the oracle's)."""
+    import paper_2608_26004_amd as asp
+    import torch
+    from parity_util import make_xvocab, to_device
+    n, B, K, V, Vd = 61, 131073, 63, 2, 3
+    x = synth.generate(B=n, K=K, V=V, dtype="bf16", rho=0.1, tau=("alternate", 0.0, 0.9), seed=17)
+    ad, bd, vm, mx = make_xvocab(x, Vd, 1.0, seed=2)
+    small = run_gpu(mx, vocab=(ad, bd, vm), want_gate=False)
+    _note(compare(mx, small, label="xvocab one launch"))
+    pick = torch.arange(B, device="cuda") % n
+    args = [to_device(v)[pick].contiguous() for v in (mx.t, ad, bd, mx.draft_tokens, mx.draft_probs, mx.uniforms,
+                                                      mx.temperature)]
+    acc, nxt, flp = asp.fuse_verify(*args, vocab_map=to_device(vm), workspace=asp.Workspace(torch.device("cuda")))
+    torch.cuda.synchronize()
+    for got, ref in zip((acc, nxt, flp), small[:3]):
+        assert torch.equal(got, to_device(ref)[pick])
+
+
 # ----------------------------------------------------------- early exit --
 def _check_early_exit(x, ee, **kw):
     """Early exit against the full read of the same call (same kernels on
