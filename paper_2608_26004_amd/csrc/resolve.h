@@ -746,43 +746,6 @@ DEV void pass2_item(const KArgs& A, int req, int sub, Smem& sm) {
 // Sub-block sums a lane of the pick holds at once.
 constexpr int kPickRun = 8;
 
-// Where a cross-family call's pass-2 kernel left its sums: [rows][T][nsub]
-// weight sums and [rows][T] divergence partials, T tiles per row, written by
-// an earlier kernel (no tags); a sub-block is kXSub consecutive tokens.
-struct XPass2 { float* sums; const float* jpart; int T, nsub; };
-
-// The sums of row `row`'s sub-blocks, each over the row's tiles in order, into
-// the row's first tile.  Whole workgroup, a thread per sub-block: consecutive
-// threads read consecutive sums, kPickTiles tiles at once.  (One wave reading
-// runs of kPickRun sub-blocks per lane, tile after tile, took most of a small call with
-// many tiles: B = 2, K = 4, V = 256000 fp32, 32 tiles.)
-constexpr int kPickTiles = 16;
-DEV void fold_sub_tiles(const XPass2& xp, size_t row) {
-  float* p = xp.sums + row * xp.T * xp.nsub;
-  for (int s = wave_id() * 64 + lane_id(); s < xp.nsub; s += kThreads) {
-    float acc = 0.0f;
-    for (int t0 = 0; t0 < xp.T; t0 += kPickTiles) {
-      float v[kPickTiles];
-      #pragma unroll
-      for (int k = 0; k < kPickTiles; ++k) v[k] = p[(size_t)min(t0 + k, xp.T - 1) * xp.nsub + s];
-      #pragma unroll
-      for (int k = 0; k < kPickTiles; ++k) acc += t0 + k < xp.T ? v[k] : 0.0f;
-    }
-    p[s] = acc;
-  }
-  __syncthreads();
-}
-// Sub-blocks [s0, s0 + n) of the folded sums; the other entries of v are zero.
-DEV void load_sub_tiles(const XPass2& xp, size_t row, int s0, int n, float (&v)[kPickRun]) {
-  // (a lane without sub-blocks reads the row's first and drops them)
-  const float* p = xp.sums + row * xp.T * xp.nsub;
-  #pragma unroll
-  for (int j = 0; j < kPickRun; ++j) {
-    const float x = p[j < n ? s0 + j : 0];
-    v[j] = j < n ? x : 0.0f;
-  }
-}
-
 // The tagged slots of sub-blocks [s0, s0 + n) (n <= kPickRun) of pass-2
 // record area rec, requested at once and polled until all are in (bounded;
 // ok cleared on a timeout); the other entries of v are zero.
@@ -818,16 +781,13 @@ DEV void load_sub_run(const KArgs& A, const uint64_t* rec, int s0, int n, float 
 // weight; otherwise the element's index, and, when the scan itself found it,
 // sm.flags[2] = 1 and its logit (f for drafts, t for the bonus row) in
 // sm.dd[3].  Whole workgroup.
-// kXv: a cross-family call, whose sub-blocks are 512 consecutive verifier
-// tokens, 8 per lane, gathered through the map.
-template <int DT, int DM, bool kXv>
-DEV int cdf_pick(const KArgs& A, int req, int i, double u, bool bonus, Smem& sm, bool& ok, const XPass2& xp) {
-  constexpr int VE = kXv ? 8 : Elem<DT>::VE;
+template <int DT, int DM>
+DEV int cdf_pick(const KArgs& A, int req, int i, double u, bool bonus, Smem& sm, bool& ok) {
+  constexpr int VE = Elem<DT>::VE;
   const int lane = lane_id(), w = wave_id();
-  if (kXv) fold_sub_tiles(xp, (size_t)(req * (A.K + 1) + i));
   if (w == 0) {
     const RowGeo g = row_span<DT>(A, req * (A.K + 1) + i);
-    const int nsub = kXv ? xp.nsub : A.S * kSubPerChunk;
+    const int nsub = A.S * kSubPerChunk;
     // lane l holds sub-blocks [l * per, l * per + per) in runs of kPickRun
     const int per = (nsub + 63) / 64;
     const int nrun = (per + kPickRun - 1) / kPickRun;
@@ -835,13 +795,9 @@ DEV int cdf_pick(const KArgs& A, int req, int i, double u, bool bonus, Smem& sm,
     const uint64_t* rec = p2_rec(A, req, i, 0);
     float v[kPickRun];
     double lsum = 0.0;
-    auto load_run = [&](int a, int n) {
-      if (kXv) load_sub_tiles(xp, (size_t)g.row, a, n, v);
-      else load_sub_run(A, rec, a, n, v, ok);
-    };
     for (int q = 0; q < nrun; ++q) {
       const int a = min(s0 + q * kPickRun, s1);
-      load_run(a, min(kPickRun, s1 - a));
+      load_sub_run(A, rec, a, min(kPickRun, s1 - a), v, ok);
       #pragma unroll
       for (int j = 0; j < kPickRun; ++j) lsum += (double)v[j];
     }
@@ -862,7 +818,7 @@ DEV int cdf_pick(const KArgs& A, int req, int i, double u, bool bonus, Smem& sm,
         double run = excl;
         for (int q = 0; q < nrun; ++q) {
           const int a = min(s0 + q * kPickRun, s1);
-          if (nrun > 1) load_run(a, min(kPickRun, s1 - a));
+          if (nrun > 1) load_sub_run(A, rec, a, min(kPickRun, s1 - a), v, ok);
           #pragma unroll
           for (int j = 0; j < kPickRun; ++j) {
             const double nx = run + (double)v[j];
@@ -887,59 +843,34 @@ DEV int cdf_pick(const KArgs& A, int req, int i, double u, bool bonus, Smem& sm,
         // lane l scans vector l of the sub-block
         const uint32_t* cst = sm.rows[i];
         const ResidConst rk = resid_const(A, cst);
-        float x[VE], xt[VE], xa[VE], xb[VE];
-        long long first;                     // flat index of the lane's first element
-        if constexpr (kXv) {
-          const int x0 = sel * 64 * VE + lane * VE;
-          XPlace pl[VE];
-          first = g.e0 + x0;
-          #pragma unroll
-          for (int e = 0; e < VE; ++e) {
-            pl[e] = map_place(A.vmap, g.row, A.V, A.Vd, x0 + e, !bonus);
-            xt[e] = Elem<DT>::load_one(A.t, pl[e].t);
-            xt[e] = pl[e].in ? xt[e] : -INFINITY;
-            xa[e] = xb[e] = -INFINITY;
-          }
-          // a plain bonus row draws from t alone
-          if (!bonus) {
-            #pragma unroll
-            for (int e = 0; e < VE; ++e) {
-              xa[e] = Elem<DT>::load_one(A.a, pl[e].ab);
-              xb[e] = Elem<DT>::load_one(A.b, pl[e].ab);
-              xa[e] = pl[e].in ? xa[e] : -INFINITY;
-              xb[e] = pl[e].in ? xb[e] : -INFINITY;
-            }
-          }
+        const int ch = sel / kSubPerChunk, sub = sel % kSubPerChunk;
+        const long long sv0 = g.vbeg + (long long)ch * kChunkVec + (long long)sub * 64;
+        const long long vi = sv0 + lane;
+        const __amdgpu_buffer_rsrc_t rt = row_rsrc(A, A.t, g);
+        const __amdgpu_buffer_rsrc_t ra = row_rsrc(A, bonus ? A.t : A.a, g);
+        // a row whose a and b are equal bitwise reads a for b (same weights)
+        const bool nb = !bonus && (cst[D_STATUS] & kStNeq) != 0u;
+        const __amdgpu_buffer_rsrc_t rb = row_rsrc(A, nb ? A.b : A.t, g);
+        const uint32_t off = (uint32_t)((vi - g.vbeg) * 16);
+        u4 vt = buf_load(rt, off);
+        u4 va = bonus ? vt : buf_load(ra, off);
+        u4 vb = nb ? buf_load(rb, off) : u4{0, 0, 0, 0};
+        if (has_tail(A, sv0, sv0 + 64)) {
+          fix_vec<DT>(A, g, A.t, vi, vt);
+          if (!bonus) fix_vec<DT>(A, g, A.a, vi, va);
+          if (nb) fix_vec<DT>(A, g, A.b, vi, vb);
         } else {
-          const int ch = sel / kSubPerChunk, sub = sel % kSubPerChunk;
-          const long long sv0 = g.vbeg + (long long)ch * kChunkVec + (long long)sub * 64;
-          const long long vi = sv0 + lane;
-          first = vi * VE;
-          const __amdgpu_buffer_rsrc_t rt = row_rsrc(A, A.t, g);
-          const __amdgpu_buffer_rsrc_t ra = row_rsrc(A, bonus ? A.t : A.a, g);
-          // a row whose a and b are equal bitwise reads a for b (same weights)
-          const bool nb = !bonus && (cst[D_STATUS] & kStNeq) != 0u;
-          const __amdgpu_buffer_rsrc_t rb = row_rsrc(A, nb ? A.b : A.t, g);
-          const uint32_t off = (uint32_t)((vi - g.vbeg) * 16);
-          u4 vt = buf_load(rt, off);
-          u4 va = bonus ? vt : buf_load(ra, off);
-          u4 vb = nb ? buf_load(rb, off) : u4{0, 0, 0, 0};
-          if (has_tail(A, sv0, sv0 + 64)) {
-            fix_vec<DT>(A, g, A.t, vi, vt);
-            if (!bonus) fix_vec<DT>(A, g, A.a, vi, va);
-            if (nb) fix_vec<DT>(A, g, A.b, vi, vb);
-          } else {
-            mask_vec<DT>(A, g, vi, vt);
-            mask_vec<DT>(A, g, vi, va);
-            mask_vec<DT>(A, g, vi, vb);
-          }
-          if (!nb) vb = va;
-          #pragma unroll
-          for (int e = 0; e < VE; ++e) {
-            xt[e] = Elem<DT>::get(vt, e);
-            xa[e] = Elem<DT>::get(va, e);
-            xb[e] = Elem<DT>::get(vb, e);
-          }
+          mask_vec<DT>(A, g, vi, vt);
+          mask_vec<DT>(A, g, vi, va);
+          mask_vec<DT>(A, g, vi, vb);
+        }
+        if (!nb) vb = va;
+        float x[VE], xt[VE], xa[VE], xb[VE];
+        #pragma unroll
+        for (int e = 0; e < VE; ++e) {
+          xt[e] = Elem<DT>::get(vt, e);
+          xa[e] = Elem<DT>::get(va, e);
+          xb[e] = Elem<DT>::get(vb, e);
         }
         double vsum = 0.0;
         #pragma unroll
@@ -955,7 +886,7 @@ DEV int cdf_pick(const KArgs& A, int req, int i, double u, bool bonus, Smem& sm,
         #pragma unroll
         for (int e = 0; e < VE; ++e) {
           run += (double)x[e];
-          const int idx = (int)(first + e - g.e0);
+          const int idx = (int)(vi * VE + e - g.e0);
           if (x[e] > 0.0f && run > target && first_ok == 0x7FFFFFFF) {
             first_ok = idx;
             fx = bonus ? xt[e] : fuse_masked(xt[e], xa[e], xb[e], A.beta, A.delta_mode);
@@ -983,6 +914,143 @@ DEV int cdf_pick(const KArgs& A, int req, int i, double u, bool bonus, Smem& sm,
   }
   __syncthreads();
   return sm.flags[3];
+}
+
+// Where a cross-family call's pass-2 kernel left its sums: [rows][T][nsub] weight
+// sums and [rows][T] divergence partials, T tiles per row and nsub <= kThreads
+// sub-blocks of 2^slog consecutive tokens, written by an earlier kernel (no tags).
+struct XPass2 { const float* sums; const float* jpart; int T, nsub, slog; };
+
+// The same draw for a cross-family call: the sub-blocks' sums, each over the row's
+// tiles in order, locate the sub-block, and the workgroup scans it, kTok tokens a
+// thread gathered through the map.
+// The sums of one sub-block over the tiles, N of them in flight.
+template <int N>
+DEV double fold_tiles(const float* p, int T, int nsub) {
+  double acc = 0.0;
+  for (int t0 = 0; t0 < T; t0 += N) {
+    float v[N];
+    #pragma unroll
+    for (int k = 0; k < N; ++k) v[k] = p[(size_t)min(t0 + k, T - 1) * nsub];
+    #pragma unroll
+    for (int k = 0; k < N; ++k) acc += t0 + k < T ? (double)v[k] : 0.0;
+  }
+  return acc;
+}
+template <int DT, int DM>
+DEV int xv_cdf_pick(const KArgs& A, int req, int i, double u, bool bonus, Smem& sm, const XPass2& xp) {
+  constexpr int kTok = 4;   // 1024 tokens, the usual sub-block, at once
+  const int lane = lane_id(), w = wave_id(), tid = w * 64 + lane;
+  const RowGeo g = row_span<DT>(A, req * (A.K + 1) + i);
+  if (tid < xp.nsub) {
+    const float* p = xp.sums + (size_t)g.row * xp.T * xp.nsub + tid;
+    sm.dw[tid] = xp.T <= 4 ? fold_tiles<4>(p, xp.T, xp.nsub)
+                           : (xp.T <= 16 ? fold_tiles<16>(p, xp.T, xp.nsub) : fold_tiles<32>(p, xp.T, xp.nsub));
+  }
+  __syncthreads();
+  if (w == 0) {
+    // lane l holds sub-blocks 4l .. 4l + 3; the sub-block: the first with weight
+    // whose cumulative sum passes the target, else (rounding left the target at
+    // the total) the last one with weight
+    constexpr int kPer = kThreads / 64;
+    double v[kPer], own = 0.0, incl, excl;
+    #pragma unroll
+    for (int e = 0; e < kPer; ++e) {
+      v[e] = lane * kPer + e < xp.nsub ? sm.dw[lane * kPer + e] : 0.0;
+      own += v[e];
+    }
+    wave_scan_d(own, incl, excl);
+    const double total = readlane_d(incl, 63), target = u * total;
+    int cand = 0x7FFFFFFF, last = -1;
+    double run = excl, cb = 0.0, lb = 0.0;
+    #pragma unroll
+    for (int e = 0; e < kPer; ++e) {
+      const double nx = run + v[e];
+      if (v[e] > 0.0 && nx > target && cand == 0x7FFFFFFF) { cand = lane * kPer + e; cb = run; }
+      if (v[e] > 0.0) { last = lane * kPer + e; lb = run; }
+      run = nx;
+    }
+    int sel = wave_min_i(cand);
+    const bool found = sel != 0x7FFFFFFF;
+    if (!found) {
+      const int neg = wave_min_i(last >= 0 ? -last : 0x7FFFFFFF);
+      sel = neg == 0x7FFFFFFF ? -1 : -neg;
+    }
+    if (sel >= 0 && lane == sel / kPer) sm.dd[4] = found ? cb : lb;
+    if (lane == 0) {
+      sm.dd[5] = target;
+      sm.flags[2] = 0;
+      sm.flags[4] = sel;
+    }
+  }
+  __syncthreads();
+  const int sel = sm.flags[4];
+  if (sel < 0) return -1;
+  const double target = sm.dd[5];
+  double run0 = sm.dd[4];
+  const uint32_t* cst = sm.rows[i];
+  const ResidConst rk = resid_const(A, cst);
+  const int end = (int)min((long long)(sel + 1) << xp.slog, (long long)A.V);
+  int last_pos = -1;
+  for (int b0 = sel << xp.slog; b0 < end; b0 += kThreads * kTok) {
+    const int x0 = b0 + tid * kTok;
+    XPlace pl[kTok];
+    float x[kTok], xt[kTok], xa[kTok], xb[kTok];
+    #pragma unroll
+    for (int e = 0; e < kTok; ++e) {
+      pl[e] = map_place(A.vmap, g.row, A.V, A.Vd, x0 + e < end ? x0 + e : -1, !bonus);
+      xt[e] = Elem<DT>::load_one(A.t, pl[e].t);
+      xt[e] = pl[e].in ? xt[e] : -INFINITY;
+      xa[e] = xb[e] = -INFINITY;
+    }
+    // a plain bonus row draws from t alone
+    if (!bonus) {
+      #pragma unroll
+      for (int e = 0; e < kTok; ++e) {
+        xa[e] = Elem<DT>::load_one(A.a, pl[e].ab);
+        xb[e] = Elem<DT>::load_one(A.b, pl[e].ab);
+        xa[e] = pl[e].in ? xa[e] : -INFINITY;
+        xb[e] = pl[e].in ? xb[e] : -INFINITY;
+      }
+    }
+    double vsum = 0.0;
+    #pragma unroll
+    for (int e = 0; e < kTok; ++e) {
+      x[e] = bonus ? bonus_elem(xt[e], rk.c, rk.Rf) : resid_elem<DM>(xt[e], xa[e], xb[e], rk);
+      vsum += (double)x[e];
+    }
+    double vin, vex;
+    block_scan(vsum, sm, vin, vex);
+    double run = run0 + vex;
+    int first_ok = 0x7FFFFFFF;
+    float fx = 0.0f;
+    #pragma unroll
+    for (int e = 0; e < kTok; ++e) {
+      run += (double)x[e];
+      if (x[e] > 0.0f && run > target && first_ok == 0x7FFFFFFF) {
+        first_ok = x0 + e;
+        fx = bonus ? xt[e] : fuse_masked(xt[e], xa[e], xb[e], A.beta, A.delta_mode);
+      }
+      if (x[e] > 0.0f) last_pos = x0 + e;
+    }
+    double all = 0.0;
+    #pragma unroll
+    for (int q = 0; q < kWaves; ++q) all += sm.scan[q];
+    run0 += all;
+    const int pick = block_min_i(first_ok, sm);
+    if (pick != 0x7FFFFFFF) {
+      if (first_ok == pick) {
+        sm.dd[3] = (double)fx;
+        sm.flags[2] = 1;
+      }
+      __syncthreads();
+      return pick;
+    }
+  }
+  // rounding left the target past the sub-block's own sum: its last element with
+  // weight
+  const int neg = block_min_i(last_pos >= 0 ? -last_pos : 0x7FFFFFFF, sm);
+  return neg == 0x7FFFFFFF ? -1 : -neg;
 }
 
 // Argmax of the emission logits of a row by a full scan (whole workgroup); only
@@ -1076,7 +1144,9 @@ DEV void pick_item(const KArgs& A, int req, Smem& sm, const XPass2& xp = XPass2{
   if (samp) {
     const bool bonus = j == K && !A.fuse_bonus;   // weights from t alone
     const double u = (double)uK;
-    int pick = cdf_pick<DT, DM, kXv>(A, req, j, u, bonus, sm, ok, xp);
+    int pick;
+    if constexpr (kXv) pick = xv_cdf_pick<DT, DM>(A, req, j, u, bonus, sm, xp);
+    else pick = cdf_pick<DT, DM>(A, req, j, u, bonus, sm, ok);
     const RowGeo g = row_span<DT>(A, req * (K + 1) + j);
     const bool have_x = pick >= 0 && sm.flags[2] != 0;
     if (pick < 0) pick = row_argmax<DT>(A, g, bonus, sm);

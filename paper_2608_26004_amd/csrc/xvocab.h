@@ -35,9 +35,30 @@
 
 namespace asym {
 
-constexpr int kXUnit = 1024;          // verifier tokens per unit of the lists' index
-constexpr int kXSub = 512;            // verifier tokens per pass-2 sub-block (8 per lane of a wave)
-constexpr int kXSubPerUnit = kXUnit / kXSub;
+// Verifier tokens are grouped in units of 2^ulog consecutive ones, by which the
+// lists are indexed: the smallest unit that leaves at most kXUnits of them.  The
+// weight sums of pass 2 are kept per (row, tile, sub-block of 2^slog tokens): the
+// unit, or down to 1024 tokens as long as all of them take no more than kXSumBytes,
+// so that the pick, which scans one sub-block, has less to scan.  Beyond that a row's
+// sums take no more of the workspace than the pass-2 records of a plain call (T * U
+// * 4 bytes against 320 a chunk): sub-blocks of 512 tokens at any size took 316 MB
+// at B = 512, K = 8, V = Vd = 256000 fp32; a pick over units of 4096 instead of 1024
+// takes 26 us instead of 13 at B = 2.
+constexpr int kXUnitLog = 10, kXUnitLogMax = 16;
+constexpr int kXUnits = 79, kXSubs = kThreads;
+constexpr size_t kXSumBytes = 8u << 20;
+constexpr int x_unit_log(int V) {
+  int l = kXUnitLog;
+  while (((V - 1) >> l) + 1 > kXUnits && l < kXUnitLogMax) ++l;
+  return l;
+}
+constexpr int x_sub_log(int U, int ulog, size_t row_tiles) {
+  int l = ulog;
+  while (l > kXUnitLog && (U << (ulog - l + 1)) <= kXSubs &&
+         row_tiles * (size_t)(U << (ulog - l + 1)) * 4 <= kXSumBytes) --l;
+  return l;
+}
+static_assert(((4194297 - 1) >> x_unit_log(4194297)) + 1 <= kXUnits, "the longest row has too many units");
 constexpr int kXBatch = 8;            // entries per thread and step
 
 constexpr int x_log2(int n) { return n <= 1 ? 0 : 1 + x_log2(n / 2); }
@@ -48,7 +69,7 @@ template <int DT> struct XTileBase {
   static constexpr int kN = kBytes / (DT == ASYMSPEC_BF16 ? 4 : 8);   // drafter ids per tile
   using Entry = XEntry<x_log2(kN)>;
   static constexpr int kSpan = (int)Entry::kSpan;
-  static_assert(kSpan % kXUnit == 0, "a span of tokens ends with a unit of the lists");
+  static_assert(kSpan % (1 << kXUnitLogMax) == 0, "a span of tokens ends with a unit");
   static constexpr int kVec = kN / (DT == ASYMSPEC_BF16 ? 8 : 4) / kThr;   // staged vectors per thread and stream
 };
 template <int DT> struct XTile;
@@ -69,111 +90,151 @@ template <> struct XTile<ASYMSPEC_FP32> : XTileBase<ASYMSPEC_FP32> {
 
 struct XArgs {
   uint32_t* list;     // entries of every tile, tile after tile
-  int32_t* cnt;       // [T][U] entries per tile and unit
+  int32_t* cnt;       // [U][T] entries per unit and tile
   int32_t* idx;       // [T][U + 1] first entry of tile tl in unit u; [U] the tile's end
   float* sums;        // [rows][T][nsub] pass-2 weight sums
   float* jpart;       // [rows][T] pass-2 divergence partials
   int32_t* work;      // [1 + rows] number of rows with a pass-2 task, then those rows
   int T, U, nsub;
+  int ulog, slog;     // 2^ulog tokens per unit, 2^slog per sub-block
+  int tlog;           // 2^tlog >= T
   int r0, r1;         // rows of each request this launch covers
   unsigned b0;        // first of its blocks (a launch holds fewer than 2^32 threads)
 };
 
 // ------------------------------------------------------------------- lists
-// One workgroup per unit of kXUnit tokens, 256 of them per wave.
+// One workgroup per unit, each wave a run of consecutive tokens of it.  The work
+// per token does not grow with the number of tiles: lanes with the same tile find
+// each other with one ballot per bit of the tile's number.  B = 2, K = 4, V = 256000,
+// Vd = 250000 fp32 (31 tiles): count 3.8 and fill 7.1 us, where 250 workgroups that
+// looped over the tiles and summed all counts took 6.0 and 21.2.
 constexpr int kXMaxT = 256;                 // tiles of a row (a row has at most 256 chunks)
-constexpr int kXPerWave = kXUnit / kWaves;
-constexpr int kXK = kXPerWave / 64;
+constexpr int kXListThr = 1024, kXListWv = kXListThr / 64;
+constexpr int kXK = 4;                      // tokens per lane at once
 
-// This lane's kXK drafter ids of unit u (-1: not shared).
-DEV void xv_ids(const KArgs& A, int u, int w, int lane, int (&j)[kXK]) {
+// The wave's first token of unit u, and its steps of 64 tokens.
+DEV int xv_first(const XArgs& X, int u, int w) { return (u << X.ulog) + w * ((1 << X.ulog) / kXListWv); }
+DEV int xv_steps(const XArgs& X) { return (1 << X.ulog) / kXListThr; }
+
+// This lane's drafter ids at steps [k0, k0 + kXK) of the wave (-1: none).
+DEV void xv_ids(const KArgs& A, const XArgs& X, int x0, int k0, int lane, int (&j)[kXK]) {
   #pragma unroll
   for (int k = 0; k < kXK; ++k) {
-    const int x = u * kXUnit + w * kXPerWave + k * 64 + lane;
-    const int v = x < A.V ? A.vmap[x] : -1;
-    j[k] = (v >= 0 && v < A.Vd) ? v : -1;
+    const int x = x0 + (k0 + k) * 64 + lane;
+    j[k] = k0 + k < xv_steps(X) ? map_id(A.vmap, A.V, A.Vd, x) : -1;
   }
 }
-// Entries per tile among the wave's tokens, into n[wave][tile].
+// Entries per tile among the wave's tokens, into its row n of LDS (zeros before).
 template <int DT>
-DEV void xv_wave_counts(const XArgs& X, const int (&j)[kXK], int lane, int* n) {
-  for (int t = 0; t < X.T; ++t) {
-    int c = 0;
+DEV void xv_wave_counts(const KArgs& A, const XArgs& X, int x0, int lane, int* n) {
+  for (int k0 = 0; k0 < xv_steps(X); k0 += kXK) {
+    int j[kXK];
+    xv_ids(A, X, x0, k0, lane, j);
     #pragma unroll
-    for (int k = 0; k < kXK; ++k) c += __popcll(__ballot(j[k] >= 0 && j[k] / XTile<DT>::kN == t));
-    if (lane == 0) n[t] = c;
+    for (int k = 0; k < kXK; ++k)
+      if (j[k] >= 0) __hip_atomic_fetch_add(n + j[k] / XTile<DT>::kN, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
   }
 }
 
 // count: the unit's entries per tile.  (Also clears the pass-2 work list.)
 template <int DT>
-__global__ __launch_bounds__(kThreads) void xv_count_kernel(KArgs A, XArgs X) {
-  __shared__ int n[kWaves][kXMaxT];
-  const int u = (int)blockIdx.x, lane = lane_id(), w = wave_id();
-  if (u == 0 && threadIdx.x == 0) X.work[0] = 0;
-  int j[kXK];
-  xv_ids(A, u, w, lane, j);
-  xv_wave_counts<DT>(X, j, lane, n[w]);
+__global__ __launch_bounds__(kXListThr) void xv_count_kernel(KArgs A, XArgs X) {
+  __shared__ int n[kXListWv][kXMaxT];
+  const int u = (int)blockIdx.x, tid = (int)threadIdx.x, lane = lane_id(), w = wave_id();
+  if (u == 0 && tid == 0) X.work[0] = 0;
+  for (int i = tid; i < kXListWv * kXMaxT; i += kXListThr) (&n[0][0])[i] = 0;
   __syncthreads();
-  for (int t = (int)threadIdx.x; t < X.T; t += kThreads) {
+  xv_wave_counts<DT>(A, X, xv_first(X, u, w), lane, n[w]);
+  __syncthreads();
+  if (tid < X.T) {
     int c = 0;
     #pragma unroll
-    for (int q = 0; q < kWaves; ++q) c += n[q][t];
-    X.cnt[(size_t)t * X.U + u] = c;
+    for (int q = 0; q < kXListWv; ++q) c += n[q][tid];
+    X.cnt[u * X.T + tid] = c;
   }
 }
 
 // fill: where the unit's entries of every tile start (after the tiles before,
 // and after the units before in the tile), then the entries in token order.
 template <int DT>
-__global__ __launch_bounds__(kThreads) void xv_fill_kernel(KArgs A, XArgs X) {
-  __shared__ int n[kWaves][kXMaxT], all[kXMaxT], before[kXMaxT];
-  const int u = (int)blockIdx.x, lane = lane_id(), w = wave_id();
-  int j[kXK];
-  xv_ids(A, u, w, lane, j);
-  // 16 lanes per tile, 8 counts a lane at once (a wave per tile waited for each
-  // tile's counts in turn: 26 us of a call with 32 tiles and 250 units)
-  const int sub = lane & 15;
-  for (int t0 = 0; t0 < X.T; t0 += 4 * kWaves) {
-    const int t = t0 + w * 4 + (lane >> 4);
-    const int32_t* c = X.cnt + (size_t)min(t, X.T - 1) * X.U;
-    int s = 0, f = 0;
-    for (int q0 = 0; q0 < X.U; q0 += 128) {
-      int v[8];
-      #pragma unroll
-      for (int k = 0; k < 8; ++k) v[k] = c[min(q0 + k * 16 + sub, X.U - 1)];
-      #pragma unroll
-      for (int k = 0; k < 8; ++k) {
-        const int q = q0 + k * 16 + sub;
-        s += q < X.U ? v[k] : 0;
-        f += q < u ? v[k] : 0;
-      }
-    }
-    s = row16_add(s);
-    f = row16_add(f);
-    if (sub == 0 && t < X.T) { all[t] = s; before[t] = f; }
-  }
-  xv_wave_counts<DT>(X, j, lane, n[w]);
+__global__ __launch_bounds__(kXListThr) void xv_fill_kernel(KArgs A, XArgs X) {
+  __shared__ int n[kXListWv][kXMaxT], all[kXMaxT], before[kXMaxT];
+  const int u = (int)blockIdx.x, tid = (int)threadIdx.x, lane = lane_id(), w = wave_id();
+  for (int i = tid; i < kXListWv * kXMaxT; i += kXListThr) (&n[0][0])[i] = 0;
+  if (tid < kXMaxT) all[tid] = before[tid] = 0;
   __syncthreads();
-  int start = 0;
-  for (int t = 0; t < X.T; ++t) {
-    int at = start + before[t];
-    if (w == 0 && lane == 0) {
-      X.idx[(size_t)t * (X.U + 1) + u] = at;
-      if (u == 0) X.idx[(size_t)t * (X.U + 1) + X.U] = start + all[t];
+  const int x0 = xv_first(X, u, w);
+  xv_wave_counts<DT>(A, X, x0, lane, n[w]);
+  #pragma unroll 4
+  for (int i = tid; i < X.U << X.tlog; i += kXListThr) {
+    const int t = i & ((1 << X.tlog) - 1), q = i >> X.tlog;
+    const int c = t < X.T ? X.cnt[q * X.T + t] : 0;
+    if (c != 0) {
+      __hip_atomic_fetch_add(all + t, c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      if (q < u) __hip_atomic_fetch_add(before + t, c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
-    for (int q = 0; q < w; ++q) at += n[q][t];
+  }
+  __syncthreads();
+  if (w == 0) {
+    // lane l: tiles 4l .. 4l + 3, after the tiles before
+    constexpr int kPer = kXMaxT / 64;
+    int own = 0;
+    #pragma unroll
+    for (int e = 0; e < kPer; ++e) own += all[lane * kPer + e];
+    int incl = own;
+    #pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int y = __shfl_up(incl, o, 64);
+      if (lane >= o) incl += y;
+    }
+    int start = incl - own;
+    #pragma unroll
+    for (int e = 0; e < kPer; ++e) {
+      const int t = lane * kPer + e, len = all[t];
+      before[t] += start;
+      if (t < X.T) {
+        X.idx[t * (X.U + 1) + u] = before[t];
+        if (u == 0) X.idx[t * (X.U + 1) + X.U] = start + len;
+      }
+      start += len;
+    }
+  }
+  __syncthreads();
+  if (tid < X.T) {
+    // the waves' runs in order
+    int at = before[tid];
+    #pragma unroll
+    for (int q = 0; q < kXListWv; ++q) {
+      const int c = n[q][tid];
+      n[q][tid] = at;
+      at += c;
+    }
+  }
+  __syncthreads();
+  const unsigned long long lt = (1ull << lane) - 1ull;
+  for (int k0 = 0; k0 < xv_steps(X); k0 += kXK) {
+    int j[kXK];
+    xv_ids(A, X, x0, k0, lane, j);
     #pragma unroll
     for (int k = 0; k < kXK; ++k) {
-      const bool in = j[k] >= 0 && j[k] / XTile<DT>::kN == t;
-      const unsigned long long m = __ballot(in);
-      const uint32_t x = (uint32_t)(u * kXUnit + w * kXPerWave + k * 64 + lane);
-      if (in)
-        X.list[at + __popcll(m & ((1ull << lane) - 1ull))] =
-            XTile<DT>::Entry::make(x, (uint32_t)(j[k] - t * XTile<DT>::kN));
-      at += __popcll(m);
+      const bool in = j[k] >= 0;
+      const int t = in ? j[k] / XTile<DT>::kN : 0;
+      // the lanes with an entry in the same tile
+      unsigned long long m = __ballot(in);
+      for (int b = 0; b < X.tlog; ++b) {
+        const bool bit = ((t >> b) & 1) != 0;
+        const unsigned long long s = __ballot(bit);
+        m &= bit ? s : ~s;
+      }
+      const int at = in ? n[w][t] : 0;
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // every lane has read its place
+      if (in) {
+        const uint32_t x = (uint32_t)(x0 + (k0 + k) * 64 + lane);
+        X.list[at + __popcll(m & lt)] = XTile<DT>::Entry::make(x, (uint32_t)(j[k] - t * XTile<DT>::kN));
+        if ((m & lt) == 0) n[w][t] = at + __popcll(m);
+      }
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     }
-    start += all[t];
   }
 }
 
@@ -296,7 +357,7 @@ DEV void xv_bounds(const XArgs& X, const XItem& it, XSmem<DT>& sm) {
   const int h = (int)threadIdx.x;
   if (h <= it.nhi && h < 64) {
     const int32_t* ix = X.idx + (size_t)it.tile * (X.U + 1);
-    sm.q[h] = ix[h * (XTile<DT>::kSpan / kXUnit)] - ix[0];
+    sm.q[h] = ix[h * (XTile<DT>::kSpan >> X.ulog)] - ix[0];
   }
 }
 
@@ -606,8 +667,8 @@ void xv_pass2_kernel(KArgs A, XArgs X) {
     __syncthreads();
     xv_bounds_in<DT>(it, sm);
     float* sums = X.sums + ((size_t)it.row * X.T + tile) * X.nsub;
-    int cur = u0 * kXSubPerUnit;
-    const int send = u1 * kXSubPerUnit;
+    int cur = u0 << (X.ulog - X.slog);
+    const int send = u1 << (X.ulog - X.slog);
     JsdAcc accj{0.0f, 0.0f};
     float acc = 0.0f;
     for (int p0 = pa; p0 < pe; p0 += 64 * kXBatch) {
@@ -633,7 +694,7 @@ void xv_pass2_kernel(KArgs A, XArgs X) {
           float v = dr ? resid_elem<DM>(xt[k], xa, xb, rk) : bonus_elem(xt[k], rk.c, rk.Rf);
           v = in ? v : 0.0f;
           // lanes past the end follow the last token
-          const int sub = in ? x[k] / kXSub : 0x7FFFFFFF;
+          const int sub = in ? x[k] >> X.slog : 0x7FFFFFFF;
           // (uniform) the last sub-block among the step's tokens
           const int last = __builtin_amdgcn_readlane(sub, min(63, pe - 1 - (p0 + k * 64)));
           while (cur < last) {
@@ -670,7 +731,7 @@ void xv_pass2_kernel(KArgs A, XArgs X) {
 template <int DT, int DM>
 __global__ __launch_bounds__(kThreads) void xv_pick_kernel(KArgs A, XArgs X) {
   __shared__ Smem sm;
-  XPass2 src{X.sums, X.jpart, X.T, X.nsub};
+  const XPass2 src{X.sums, X.jpart, X.T, X.nsub, X.slog};
   pick_item<DT, DM, true>(A, (int)blockIdx.x, sm, src);
 }
 

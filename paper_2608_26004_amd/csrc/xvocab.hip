@@ -15,9 +15,11 @@ template <>
 size_t xv_layout<ASYMSPEC_PART_DT>(int B, int K, int V, int Vd, XLayout& L) {
   constexpr int kN = XTile<ASYMSPEC_PART_DT>::kN;
   L.T = (Vd + kN - 1) / kN;
-  L.U = (V + kXUnit - 1) / kXUnit;
-  L.nsub = L.U * kXSubPerUnit;
+  L.ulog = x_unit_log(V);
+  L.U = ((V - 1) >> L.ulog) + 1;
   const size_t rows = (size_t)B * (K + 1);
+  L.slog = x_sub_log(L.U, L.ulog, rows * L.T);
+  L.nsub = L.U << (L.ulog - L.slog);
   size_t off = 0;
   auto take = [&](size_t n) { const size_t at = off; off = (off + n + 255) / 256 * 256; return at; };
   L.off_list = take((size_t)V * 4);
@@ -38,7 +40,9 @@ static hipError_t launch(KArgs A, const XLayout& L, char* base, int ee_rows, int
   X.sums = (float*)(base + L.off_sums);
   X.jpart = (float*)(base + L.off_jpart);
   X.work = (int32_t*)(base + L.off_work);
-  X.T = L.T; X.U = L.U; X.nsub = L.nsub;
+  X.T = L.T; X.U = L.U; X.nsub = L.nsub; X.ulog = L.ulog; X.slog = L.slog;
+  X.tlog = 0;
+  while ((1 << X.tlog) < X.T) ++X.tlog;
   const int nrow = A.K + 1;
   A.S = X.T;                   // records per row
   A.full_poll = 1;
@@ -58,8 +62,8 @@ static hipError_t launch(KArgs A, const XLayout& L, char* base, int ee_rows, int
       hipLaunchKernelGGL((xv_stats_kernel<DT, DM>), dim3((unsigned)std::min(kMost, n - b0)), dim3(kThr), 0, st, A, X);
     }
   };
-  hipLaunchKernelGGL((xv_count_kernel<DT>), dim3(L.U), dim3(kThreads), 0, st, A, X);
-  hipLaunchKernelGGL((xv_fill_kernel<DT>), dim3(L.U), dim3(kThreads), 0, st, A, X);
+  hipLaunchKernelGGL((xv_count_kernel<DT>), dim3(L.U), dim3(kXListThr), 0, st, A, X);
+  hipLaunchKernelGGL((xv_fill_kernel<DT>), dim3(L.U), dim3(kXListThr), 0, st, A, X);
   stats(0, A.sc.G);
   if (A.sc.ee) {
     hipLaunchKernelGGL((xv_decide_kernel<DT>), dim3(A.B), dim3(kThreads), 0, st, A, X, 1);

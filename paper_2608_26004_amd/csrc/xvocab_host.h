@@ -12,7 +12,8 @@ namespace asym {
 
 // Places of a cross-family call's own arrays within its part of the workspace.
 struct XLayout {
-  int T, U, nsub;   // drafter tiles, list units, pass-2 sub-blocks per row
+  int T, U, nsub;   // drafter tiles; list units and pass-2 sub-blocks per row
+  int ulog, slog;   // of 2^ulog and 2^slog verifier tokens
   size_t off_list, off_cnt, off_idx, off_sums, off_jpart, off_work;
 };
 

@@ -52,6 +52,22 @@ def test_workspace_size():
     assert asp.workspace_size(1, 1, 2097150, asp.FP32) == 0
 
 
+@pytest.mark.parametrize("B,K,V,Vd,dt", [
+    (512, 8, 256000, 256000, asp.BF16), (512, 8, 256000, 256000, asp.FP32), (128, 6, 151936, 128256, asp.BF16),
+    (64, 3, 32000, 250000, asp.FP32), (300, 2, 4194297, 4194297, asp.BF16), (1, 0, 1, 1, asp.BF16)])
+def test_workspace_size_xvocab(B, K, V, Vd, dt):
+    """A cross-family workspace is a plain call's for the longer vocabulary, the
+    map's lists with their index, the divergence partials and the work list,
+    and at most 8 MiB of finer pass-2 sums: not the product of the two
+    vocabularies per row."""
+    lib = asp.load_library()
+    rows, tiles = B * (K + 1), -(-Vd // (16384 if dt == asp.BF16 else 8192))
+    size = lib.asymspec_workspace_size_xvocab(B, K, V, Vd, dt)
+    plain = asp.workspace_size(B, K, max(V, Vd), dt)
+    lists = 4 * V + 2 * 4 * tiles * 80 + 4 * rows * (tiles + 1) + 4 * Vd
+    assert plain < size <= plain + lists + (8 << 20) + 4096
+
+
 def _call(**over):
     lib = asp.load_library()
     fake = 1 << 20          # 16-B and 256-B aligned fake device addresses

@@ -602,7 +602,7 @@ def test_xvocab_workload_1(gpu):
 def test_xvocab_tile_edges(gpu, dtype, V, Vd, frac):
     """Drafter vocabularies around a tile (16384 bf16 or 8192 fp32 ids), odd
     ones (rows then start between 4-byte boundaries), verifier vocabularies
-    around a unit of the lists (1024 tokens) and past the tokens that a
+    around 1024 tokens (the smallest unit of the lists) and past the tokens that a
     list entry tells apart (196608 or 393216), and tiles with few or no entries; greedy
     and sampling requests, the divergence of every row, and early exit with
     the full read's outputs."""
@@ -622,16 +622,39 @@ def test_xvocab_tile_edges(gpu, dtype, V, Vd, frac):
     ("bf16", 3000, 15 * 16384, 0.9), ("bf16", 2049, 16 * 16384, 1.0), ("bf16", 140001, 16 * 16384 + 1, 0.6),
     ("fp32", 132097, 33 * 8192 - 1, 0.5)])
 def test_xvocab_many_tiles(gpu, dtype, V, Vd, frac):
-    """15, 16, 17 and 33 tiles a row (the list kernel sums 16 tiles at once,
-    the pick folds 16 at once) and verifier vocabularies of 3, 3, 137 and 130
-    units of the lists (128 counts at once); the emission draws go through
-    the folded sums."""
+    """15, 16, 17 and 33 tiles a row (the pick folds 16 or 32 at once), small and
+    long verifier vocabularies; the emission draws go through the folded sums."""
     from parity_util import make_xvocab
     x = synth.generate(B=3, K=2, V=V, dtype=dtype, rho=("alternate", 0.7, 0.0),
                        tau=("alternate", 0.9, 0.0), seed=V % 1009)
     ad, bd, vm, mx = make_xvocab(x, Vd, frac, seed=Vd % 97)
     g = run_gpu(mx, vocab=(ad, bd, vm))
     _note(compare(mx, g, label=f"xvocab many tiles {dtype} V={V} Vd={Vd}"))
+
+
+@pytest.mark.parametrize("dtype,V,Vd,frac", [
+    ("bf16", 80896, 4 * 16384, 0.5), ("bf16", 80897, 5 * 16384, 0.5), ("bf16", 161793, 17 * 16384, 0.4),
+    ("bf16", 400001, 20001, 0.04), ("fp32", 330001, 33 * 8192, 0.3), ("fp32", 3000, 32 * 8192, 0.9),
+    ("fp32", 5000, 16 * 8192 - 3, 0.9), ("fp32", 2000, 17 * 8192, 1.0)])
+def test_xvocab_units(gpu, dtype, V, Vd, frac):
+    """Units of 1024, 2048, 4096 and 8192 verifier tokens (at most 79 a row, and
+    past 4 steps of a wave), sub-blocks of 1024 and 2048 (at most 256 a row),
+    rows of 4, 5, 16, 17, 32 and 33 tiles (the decide combines 16 or 32 records
+    in a wave, more through LDS), three spans of a list entry's token, and
+    mapped tokens that both views, or the full view alone, mask."""
+    from parity_util import make_xvocab
+    x = synth.generate(B=4, K=2, V=V, dtype=dtype, rho=("alternate", 0.7, 0.0),
+                       tau=("alternate", 0.9, 0.0), seed=V % 1009)
+    neg = np.float32(-np.inf) if dtype == "fp32" else np.uint16(0xFF80)
+    x.a[:, :, 100:140] = neg
+    x.b[:, :, 100:120] = neg
+    x.draft_tokens[:] = np.where((x.draft_tokens >= 100) & (x.draft_tokens < 140), 7, x.draft_tokens)
+    ad, bd, vm, mx = make_xvocab(x, Vd, frac, seed=Vd % 97)
+    # (a draft moved onto the shared set may have landed on a masked token)
+    d = mx.draft_tokens
+    d[(d >= 100) & (d < 140)] = np.nonzero(vm[140:] >= 0)[0][0] + 140
+    g = run_gpu(mx, vocab=(ad, bd, vm))
+    _note(compare(mx, g, label=f"xvocab units {dtype} V={V} Vd={Vd}"))
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "fp32"])
