@@ -508,6 +508,15 @@ DEV double row16_sum(double x) {
   return x + ror16_d<1>(x);
 }
 
+// The value of the lane 16 away in the same half of the wave.
+DEV int xor16_i(int x) { return __builtin_amdgcn_ds_swizzle(x, 0x401F); }
+DEV float xor16_f(float x) { return __int_as_float(xor16_i(__float_as_int(x))); }
+DEV double xor16_d(double x) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, x);
+  const uint32_t lo = (uint32_t)xor16_i((int)(uint32_t)b), hi = (uint32_t)xor16_i((int)(uint32_t)(b >> 32));
+  return __builtin_bit_cast(double, (uint64_t)lo | ((uint64_t)hi << 32));
+}
+
 // An fp64 value of one lane, in every lane.
 DEV double readlane_d(double x, int lane) {
   const uint64_t b = __builtin_bit_cast(uint64_t, x);

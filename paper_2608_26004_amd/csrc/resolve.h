@@ -181,15 +181,17 @@ DEV void classify_row(const KArgs& A, const RowGeo& g, const Gather& gq, float M
 // rejection and were not read) get placeholder blocks.  Thread (i, ch) of a
 // group of rows takes record ch of row i, so all records arrive in one round
 // trip; the row's maxima, sums, argmax and a-vs-b flag are combined (for
-// S <= 16 within the 16 lanes of a DPP row given to each row, else through
-// LDS in chunk order) and the row's first thread classifies it.  Whole
+// S <= 32 within the 16 or 32 lanes given to each row, else through LDS in
+// chunk order) and the row's first thread classifies it.  Whole
 // workgroup; S must not exceed kThreads.
 template <int DT>
 DEV void decide_request(const KArgs& A, int req, Smem& sm, int nread) {
   const int lane = lane_id(), w = wave_id(), tid = w * 64 + lane;
   const int K = A.K, S = A.S, nrow = K + 1;
-  const bool dpp = S <= 16;                     // a row's chunks in one DPP row
-  const int stride = dpp ? 16 : S;              // lanes per row
+  // a row's chunks in one DPP row or two of them (17 to 32 chunks through LDS
+  // took 11.5 us of a cross-family call with 31 tiles, 9.0 this way)
+  const bool dpp = S <= 32, two = S > 16;
+  const int stride = dpp ? (two ? 32 : 16) : S; // lanes per row
   const int rpg = kThreads / stride;            // rows per group
   const int li = tid / stride, ch = tid - li * stride;
   // the last statistics item read in list order is about the last to
@@ -236,16 +238,28 @@ DEV void decide_request(const KArgs& A, int req, Smem& sm, int nread) {
       float Rr[kSlots];
       #pragma unroll
       for (int s = 0; s < kSlots; ++s) Rr[s] = row16_max(have ? payf(r[R1_R + s]) : kFloorM);
-      const float Marg = row16_max(have ? payf(r[R1_MARG]) : kFloorM);
+      float Marg = row16_max(have ? payf(r[R1_MARG]) : kFloorM);
+      if (two) {
+        #pragma unroll
+        for (int s = 0; s < kSlots; ++s) Rr[s] = fmaxf(Rr[s], xor16_f(Rr[s]));
+        Marg = fmaxf(Marg, xor16_f(Marg));
+      }
       double Sp[kSlots];
       #pragma unroll
       for (int s = 0; s < kSlots; ++s)
         Sp[s] = row16_sum(have ? (double)(payf(r[R1_S + s]) * __builtin_amdgcn_exp2f(payf(r[R1_R + s]) - Rr[s]))
                                : 0.0);
-      const double Wkl =
+      double Wkl =
           row16_sum(have ? (double)(payf(r[R1_W]) * __builtin_amdgcn_exp2f(payf(r[R1_R + sA]) - Rr[sA])) : 0.0);
-      const int arg = row16_min(have && payf(r[R1_MARG]) == Marg ? (int)pay(r[R1_ARG]) : 0x7FFFFFFF);
-      const int nq = row16_or(have ? (int)pay(r[R1_NEQ]) : 0);
+      int arg = row16_min(have && payf(r[R1_MARG]) == Marg ? (int)pay(r[R1_ARG]) : 0x7FFFFFFF);
+      int nq = row16_or(have ? (int)pay(r[R1_NEQ]) : 0);
+      if (two) {
+        #pragma unroll
+        for (int s = 0; s < kSlots; ++s) Sp[s] += xor16_d(Sp[s]);
+        Wkl += xor16_d(Wkl);
+        arg = min(arg, xor16_i(arg));
+        nq |= xor16_i(nq);
+      }
       if (have && ch == 0) classify_row<DT>(A, g, gq, Marg, Rr, Sp, Wkl, arg, nq != 0, sm.rows[i]);
       __syncthreads();
       continue;

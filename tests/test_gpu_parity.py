@@ -104,6 +104,26 @@ def test_divergence_of_logits_far_from_zero(gpu, B, tau, Vd):
     assert err <= 1e-6, err
 
 
+@pytest.mark.parametrize("dtype,V", [
+    ("fp32", 131066), ("fp32", 131070), ("fp32", 262138), ("fp32", 262142), ("bf16", 262130), ("bf16", 262138)])
+def test_decide_record_counts(gpu, dtype, V):
+    """Rows of 16, 17, 32 and 33 chunks: the decide combines up to 16 records
+    in a DPP row, up to 32 in two of them, more through LDS.  Greedy and
+    sampling requests, the KL gate's sum, and a maximum attained in two chunks 16
+    and more apart (the first index wins)."""
+    x = synth.generate(B=4, K=2, V=V, dtype=dtype, rho=("alternate", 0.6, 0.0), tau=("alternate", 0.0, 0.9),
+                       seed=V % 1013)
+    per = 8192 if dtype == "fp32" else 16384
+    top = np.float32(40.0) if dtype == "fp32" else np.uint16(0x4220)
+    for at in (2 * per + 77, V - 5):
+        x.t[0, :, at] = top
+        x.a[0, :, at] = x.b[0, :, at]
+    for mode in (0, 2):
+        g = run_gpu(x, gate_mode=mode)
+        assert g[1][0] == 2 * per + 77
+        _note(compare(x, g, gate_mode=mode, label=f"record counts {dtype} V={V} mode={mode}"))
+
+
 def test_argmax_ties_across_waves_and_chunks(gpu):
     """Greedy rows whose fused maximum is attained twice, in the runs of two
     waves of one statistics item and in two chunks: the first index wins
