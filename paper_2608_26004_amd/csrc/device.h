@@ -812,9 +812,6 @@ DEV __amdgpu_buffer_rsrc_t row_rsrc(const KArgs& A, const void* base, const RowG
   // a row past the array's end (never for a valid row index) reads nothing
   const unsigned long long rem = rbase < A.stream_bytes ? A.stream_bytes - rbase : 0ull;
   if (span > rem) span = rem;
-  // drafter rows of another vocabulary are reached through the map only:
-  // a resource over them reads zeros and touches no memory
-  if (A.vmap != nullptr && base != A.t) span = 0;
   return make_rsrc((const char*)base + rbase, span);
 }
 
@@ -844,7 +841,6 @@ template <int DT>
 DEV void fix_vec(const KArgs& A, const RowGeo& g, const void* src, long long vi, u4& v) {
   constexpr int VE = Elem<DT>::VE;
   constexpr int ES = 16 / VE;
-  if (A.vmap != nullptr && src != A.t) return;   // drafter rows: map_vecs
   const long long last_full = (long long)(A.stream_bytes / 16ull);
   if (vi >= last_full && vi < g.vend) {
     const long long n_el = (long long)(A.stream_bytes / ES);
@@ -897,12 +893,11 @@ DEV void map_vecs(const KArgs& A, const RowGeo& g, long long vi, u4& vt, u4& va,
 }
 // The emission logit of verifier token x of row g: the fused logit (-inf where
 // it is not a number), or t on a plain bonus row, which reads neither a nor b (a
-// call without drafts may bring none).
-template <int DT>
+// call without drafts may bring none).  kXv: a cross-family call.
+template <int DT, bool kXv>
 DEV float emit_logit(const KArgs& A, const RowGeo& g, int x, bool bonus) {
-  XPlace pl{x >= 0 && x < A.V, 0, 0};
-  if (A.vmap != nullptr) pl = map_place(A.vmap, g.row, A.V, A.Vd, x, !bonus);
-  else pl.t = pl.ab = g.e0 + x;
+  XPlace pl{x >= 0 && x < A.V, g.e0 + x, g.e0 + x};
+  if (kXv) pl = map_place(A.vmap, g.row, A.V, A.Vd, x, !bonus);
   if (!pl.in) return -INFINITY;
   const float t = Elem<DT>::load_one(A.t, pl.t);
   if (bonus) return t;
@@ -924,14 +919,14 @@ DEV float sload_elem(const void* base, long long idx) {
 
 // The draft token's logits and the caller's proposal probability and
 // uniform for draft row g (g.pos < K); a bonus row gets neutral values.
-template <int DT>
+template <int DT, bool kXv>
 DEV Gather sgather(const KArgs& A, const RowGeo& g) {
   Gather q{0.0f, 0.0f, 0.0f, 1.0f, 0.0f};
   if (g.pos < A.K) {
     int dtok = (int)((cptr32)(const void*)A.d)[g.req * A.K + g.pos];
     dtok = dtok < 0 ? 0 : (dtok >= A.V ? A.V - 1 : dtok);
     const long long idx = g.e0 + dtok;
-    if (A.vmap != nullptr) {
+    if (kXv) {
       // a draft outside the shared set has no mass in any view
       const int j = ((cptr32)(const void*)A.vmap)[dtok];
       if (j >= 0 && j < A.Vd) {

@@ -32,7 +32,8 @@ __global__ __launch_bounds__(kThreads) void dump_kernel(KArgs A, float* out) {
   const bool fused = i < A.K || A.fuse_bonus != 0;
   // b is a bitwise copy of a on a row whose views never differ
   const bool nb = (pay(blk[D_STATUS]) & kStNeq) != 0u;
-  full_chunk<DT, DM>(A, out, row_span<DT>(A, row), m, fused, nb, c, l2);
+  if (A.vmap != nullptr) full_chunk<DT, DM, true>(A, out, row_span<DT>(A, row), m, fused, nb, c, l2);
+  else full_chunk<DT, DM, false>(A, out, row_span<DT>(A, row), m, fused, nb, c, l2);
 }
 
 // Behind a decision kernel whose statistics items write the full rows: the rows
@@ -51,8 +52,8 @@ __global__ __launch_bounds__(kThreads) void full_rest_kernel(KArgs A) {
     if (!tag_ok(hdr[H_FULL], A.epoch) || !tag_ok(hdr[H_STATE], A.epoch) || pay(hdr[H_STATE]) == kStateFailed) continue;
     const uint64_t* blk = dec_row(A, req, i);
     const bool fused = i < A.K || A.fuse_bonus != 0;
-    full_chunk<DT, DM>(A, A.full, row_span<DT>(A, row), m, fused, (pay(blk[D_STATUS]) & kStNeq) != 0u,
-                       (double)payf(blk[D_C]), payd(blk[D_L2E_LO], blk[D_L2E_HI]));
+    full_chunk<DT, DM, false>(A, A.full, row_span<DT>(A, row), m, fused, (pay(blk[D_STATUS]) & kStNeq) != 0u,
+                              (double)payf(blk[D_C]), payd(blk[D_L2E_LO], blk[D_L2E_HI]));
   }
 }
 

@@ -131,14 +131,14 @@ DEV bool full_norm(const KArgs& A, const RowGeo& g, Smem& sm, double& l2) {
 }
 
 // Chunk m of row g read (again) and written.  nb: b differs from a somewhere in
-// the row.
-template <int DT, int DM>
+// the row.  kXv: a cross-family call, a and b gathered through the map.
+template <int DT, int DM, bool kXv>
 DEV void full_chunk(const KArgs& A, float* out, const RowGeo& g, int m, bool fused, bool nb, double c, double l2) {
   constexpr int VE = Elem<DT>::VE;
   constexpr int kPerThread = kChunkVec / kThreads;
   const __amdgpu_buffer_rsrc_t rt = row_rsrc(A, A.t, g);
-  const __amdgpu_buffer_rsrc_t ra = row_rsrc(A, A.a, g);
-  const __amdgpu_buffer_rsrc_t rb = row_rsrc(A, A.b, g);
+  const __amdgpu_buffer_rsrc_t ra = row_rsrc(A, kXv ? A.t : A.a, g);
+  const __amdgpu_buffer_rsrc_t rb = row_rsrc(A, kXv ? A.t : A.b, g);
   const long long v0 = (long long)m * kChunkVec;
   const long long c0 = g.vbeg + v0;
   const bool tail = has_tail(A, c0, c0 + kChunkVec);
@@ -150,14 +150,14 @@ DEV void full_chunk(const KArgs& A, float* out, const RowGeo& g, int m, bool fus
     if (vi >= g.vend) break;
     const uint32_t off = (uint32_t)(rel * 16);
     u4 vt = buf_load_nt(rt, off), va = vt, vb = vt;
-    if (A.vmap != nullptr) {
+    if (kXv) {
       fix_vec<DT>(A, g, A.t, vi, vt);
       map_vecs<DT>(A, g, vi, vt, va, vb, fused);
     } else if (fused) {
       va = buf_load_nt(ra, off);
       vb = nb ? buf_load_nt(rb, off) : va;
     }
-    if (tail && A.vmap == nullptr) {
+    if (tail && !kXv) {
       fix_vec<DT>(A, g, A.t, vi, vt);
       if (fused) {
         fix_vec<DT>(A, g, A.a, vi, va);

@@ -64,13 +64,15 @@ DEV void classify_row(const KArgs& A, const RowGeo& g, const Gather& gq, float M
   double thr = 0.0;
   v[D_C] = __float_as_uint(g.c);
   if (draft) {
-    const JsdConst jk = jsd_make(R[sA], lg[sA], R[sB], lg[sB], wide);
-    v[D_JRA] = __float_as_uint(jk.Ra);
-    v[D_JRB] = __float_as_uint(jk.Rb);
-    v[D_JKA] = __float_as_uint(jk.ka);
-    v[D_JKB] = __float_as_uint(jk.kb);
-    v[D_JSA] = __float_as_uint(jk.sa);
-    v[D_JSB] = __float_as_uint(jk.sb);
+    if (gm != ASYMSPEC_GATE_LAMBDA && gm != ASYMSPEC_GATE_KL) {
+      const JsdConst jk = jsd_make(R[sA], lg[sA], R[sB], lg[sB], wide);
+      v[D_JRA] = __float_as_uint(jk.Ra);
+      v[D_JRB] = __float_as_uint(jk.Rb);
+      v[D_JKA] = __float_as_uint(jk.ka);
+      v[D_JKB] = __float_as_uint(jk.kb);
+      v[D_JSA] = __float_as_uint(jk.sa);
+      v[D_JSB] = __float_as_uint(jk.sb);
+    }
     const float fd = fuse_masked(gq.t, gq.a, gq.b, A.beta, A.delta_mode);
     // gates whose D is known here, so that the row is decided at once:
     // lambda (App. B), D = lambda * Delta(d), Delta the drafter views'
@@ -184,7 +186,7 @@ DEV void classify_row(const KArgs& A, const RowGeo& g, const Gather& gq, float M
 // S <= 32 within the 16 or 32 lanes given to each row, else through LDS in
 // chunk order) and the row's first thread classifies it.  Whole
 // workgroup; S must not exceed kThreads.
-template <int DT>
+template <int DT, bool kXv>
 DEV void decide_request(const KArgs& A, int req, Smem& sm, int nread) {
   const int lane = lane_id(), w = wave_id(), tid = w * 64 + lane;
   const int K = A.K, S = A.S, nrow = K + 1;
@@ -210,7 +212,7 @@ DEV void decide_request(const KArgs& A, int req, Smem& sm, int nread) {
     #pragma unroll
     for (int j = 0; j < R1_USED; ++j) r[j] = have ? ld_tag(base + j) : ((uint64_t)A.epoch << 32);
     Gather gq{0.0f, 0.0f, 0.0f, 1.0f, 0.0f};
-    if (have && ch == 0) gq = sgather<DT>(A, row_span<DT>(A, req * nrow + i));
+    if (have && ch == 0) gq = sgather<DT, kXv>(A, row_span<DT>(A, req * nrow + i));
     const RowGeo g = row_geo<DT>(A, req * nrow + i);
     bool first = true;
     all_in = load_tagged(A, sentinel, [&]() {
@@ -412,13 +414,13 @@ DEV uint32_t load_verdict(const KArgs& A, int req, Smem& sm) {
 // the first G rows only, and a sure rejection among them (Alg. 1 stops at
 // the first rejection) means the other rows need not be read.  Both share
 // one instance of decide_request.
-template <int DT>
+template <int DT, bool kXv = false>
 DEV void decide_item(const KArgs& A, int req, Smem& sm, bool verdict) {
   const int lane = lane_id(), w = wave_id(), tid = w * 64 + lane;
   const int K = A.K, nrow = K + 1;
   int nread = nrow;
   if (verdict || (A.sc.ee && load_verdict(A, req, sm) == kVerdictSkip)) nread = A.sc.G;
-  decide_request<DT>(A, req, sm, nread);
+  decide_request<DT, kXv>(A, req, sm, nread);
   // a timed-out wait for the records: the request fails (an early-exit
   // verdict then reads every row)
   const bool failed = sm.req[R_FAIL] != 0u;
@@ -1069,12 +1071,12 @@ DEV int xv_cdf_pick(const KArgs& A, int req, int i, double u, bool bonus, Smem& 
 
 // Argmax of the emission logits of a row by a full scan (whole workgroup); only
 // used when a residual is empty (p~ equal to q in fp32).
-template <int DT>
+template <int DT, bool kXv>
 DEV int row_argmax(const KArgs& A, const RowGeo& g, bool bonus, Smem& sm) {
   float best = kFloorM;
   int bi = 0x7FFFFFFF;
   for (int x = wave_id() * 64 + lane_id(); x < A.V; x += kThreads) {
-    const float f = emit_logit<DT>(A, g, x, bonus);
+    const float f = emit_logit<DT, kXv>(A, g, x, bonus);
     if (f > best) { best = f; bi = x; }
   }
   const float M = wave_max(best);
@@ -1163,9 +1165,9 @@ DEV void pick_item(const KArgs& A, int req, Smem& sm, const XPass2& xp = XPass2{
     else pick = cdf_pick<DT, DM>(A, req, j, u, bonus, sm, ok);
     const RowGeo g = row_span<DT>(A, req * (K + 1) + j);
     const bool have_x = pick >= 0 && sm.flags[2] != 0;
-    if (pick < 0) pick = row_argmax<DT>(A, g, bonus, sm);
+    if (pick < 0) pick = row_argmax<DT, kXv>(A, g, bonus, sm);
     next = pick;
-    const float x = have_x ? (float)sm.dd[3] : emit_logit<DT>(A, g, next, bonus);
+    const float x = have_x ? (float)sm.dd[3] : emit_logit<DT, kXv>(A, g, next, bonus);
     const double c = (double)__uint_as_float(sm.rows[j][D_C]);
     const double l2 = u2d(sm.rows[j][D_L2E_LO], sm.rows[j][D_L2E_HI]);
     lpn = (float)(((double)x * c - l2) * kLn2);

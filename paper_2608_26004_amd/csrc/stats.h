@@ -402,7 +402,7 @@ DEV void stats_item(const KArgs& A, int row, int m, Smem& sm) {
       constexpr bool kFused = KindTraits<KIND>::NS == 3;
       double l2;
       if (full_norm<KindTraits<KIND>::argslot>(A, g, sm, l2))
-        full_chunk<DT, DM>(A, A.full, g, m, kFused, kFused, (double)g.c, l2);
+        full_chunk<DT, DM, false>(A, A.full, g, m, kFused, kFused, (double)g.c, l2);
     }
   }
 }

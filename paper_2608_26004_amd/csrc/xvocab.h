@@ -611,7 +611,7 @@ template <int DT>
 __global__ __launch_bounds__(kThreads) void xv_decide_kernel(KArgs A, XArgs X, int verdict) {
   __shared__ Smem sm;
   const int req = (int)blockIdx.x;
-  decide_item<DT>(A, req, sm, verdict != 0);
+  decide_item<DT, true>(A, req, sm, verdict != 0);
   if (verdict != 0 || wave_id() != 0 || sm.req[R_FAIL] != 0u || sm.req[R_FIN] != 0u) return;
   const int lane = lane_id();
   const bool task = lane <= A.K && sm.rows[lane][D_TASK] != 0u;
