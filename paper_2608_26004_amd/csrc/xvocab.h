@@ -30,6 +30,8 @@
 #ifndef ASYMSPEC_XVOCAB_H_
 #define ASYMSPEC_XVOCAB_H_
 
+#include <cstddef>
+
 #include "device.h"
 #include "resolve.h"
 
@@ -240,7 +242,7 @@ __global__ __launch_bounds__(kXListThr) void xv_fill_kernel(KArgs A, XArgs X) {
 
 // -------------------------------------------------------------------- tile
 template <int DT>
-struct XSmem {
+struct alignas(16) XSmem {
   using XT = XTile<DT>;
   // a row may start one element after a 4-byte boundary: the tile holds the
   // elements from that boundary on
@@ -253,6 +255,9 @@ struct XSmem {
   float wj[XT::kWv], wmarg[XT::kWv];
   int warg[XT::kWv], wneq[XT::kWv];
 };
+// the tile is written 16 bytes at a time
+static_assert(alignof(XSmem<ASYMSPEC_BF16>) >= sizeof(u4) && offsetof(XSmem<ASYMSPEC_BF16>, pair) == 0 &&
+              alignof(XSmem<ASYMSPEC_FP32>) >= sizeof(u4) && offsetof(XSmem<ASYMSPEC_FP32>, pair) == 0, "tile alignment");
 
 // Drafter ids [j0, j0 + n) of a row on their way into LDS: 16-byte loads from
 // the 4-byte boundary at or before the first (a and b are 4-byte aligned),
