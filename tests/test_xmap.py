@@ -4,6 +4,7 @@ brings no drafter rows (the launcher then passes t, B * V logits, in their
 place), so a plain bonus row must name no place in them."""
 
 import os
+import re
 import subprocess
 
 import pytest
@@ -61,11 +62,14 @@ def test_places_lie_in_the_arrays(driver):
 
 
 def test_plain_bonus_rows_name_no_drafter_array():
-    """The kernels' readers of single mapped tokens go through map_place or
-    emit_logit with the row's kind; none indexes a or b by the map itself."""
-    src = open(os.path.join(CSRC, "resolve.h")).read()
-    body = src[src.index("DEV int cdf_pick"):]
-    assert "map_place(A.vmap, g.row, A.V, A.Vd, x0 + e, !bonus)" in body
-    for line in body.splitlines():
-        if "load_one(A.a" in line or "load_one(A.b" in line:
-            assert ".ab)" in line, line
+    """The readers of single mapped tokens take their places from map_place with
+    the row's kind; none indexes a or b by the map itself."""
+    for name in ("resolve.h", "device.h"):
+        src = open(os.path.join(CSRC, name)).read()
+        calls = re.findall(r"map_place\(A\.vmap,[^;]*;", src)
+        assert calls, name
+        for c in calls:
+            assert re.search(r", (!bonus|ab)\);$", c), c
+        for line in src.splitlines():
+            if re.search(r"load_one\(A\.[ab],", line):
+                assert "pl.ab)" in line or "pl[e].ab)" in line, line
