@@ -112,8 +112,9 @@ typedef struct asymspec_params {
 
 /* Bytes of device workspace asymspec_fuse_verify needs for this shape
  * (0 for invalid arguments).  The workspace needs no initialisation and may be
- * reused across calls of any shape: every record the kernel exchanges between
- * workgroups is tagged with a per-call epoch.
+ * reused across calls of any shape and of every entry point: every record the
+ * kernel exchanges between workgroups is tagged with a per-call epoch, and no
+ * other word that a call leaves there can pass for a tag.
  * Calls that may run at the same time need distinct workspaces.
  * The epoch is a launch argument chosen on the host at each call, so a call
  * must not be captured into a HIP graph and replayed: every replay would
@@ -229,7 +230,9 @@ int asymspec_fuse_verify(const void* verifier_logits,
  * rows are read contiguously, tile by tile, and the mapped pairs taken from
  * LDS; the call enqueues a short sequence of kernels.
  */
-/* Workspace bytes of asymspec_fuse_verify_xvocab (0 for invalid arguments). */
+/* Workspace bytes of asymspec_fuse_verify_xvocab (0 for invalid arguments): what
+ * asymspec_workspace_size asks for the longer vocabulary, 4 bytes per verifier
+ * token, and up to 8 MiB. */
 size_t asymspec_workspace_size_xvocab(int B, int K, int V, int Vd, int dtype);
 
 int asymspec_fuse_verify_xvocab(const void* verifier_logits,

@@ -21,11 +21,12 @@
 // them read.  Measured on B = 128, K = 6, V = 151936, Vd = 128256, 109566
 // shared, bf16: 32 KiB tiles 1430 us, 64 KiB 330 us, 128 KiB (one workgroup per
 // CU, with or without the next tile prefetched in registers) 347-357 us, 321 us
-// with one batch's gathers of t in flight while the batch before is reduced;
-// element-wise gathers from global memory, with a and b in drafter order and t
-// through the inverse map, took 1070 us.  What is left is bound by the address
-// unit: 40 cache accesses per 64-lane gather of t (70% busy in the statistics,
-// VALU 55%).
+// with one batch's gathers of t in flight while the batch before is reduced,
+// 311 us now; element-wise gathers from global memory, with a and b in drafter
+// order and t through the inverse map, took 1070 us.  What is left is bound by
+// the address unit (profiles/fuse_verify_xvocab_B128_K6_V151936_Vd128256_bf16.md):
+// in the statistics, two thirds of the call, it is 65% busy and the VALU 53%, with
+// 90 M cache accesses, about 50 per 64-lane gather of t.
 
 #ifndef ASYMSPEC_XVOCAB_H_
 #define ASYMSPEC_XVOCAB_H_
