@@ -3,7 +3,9 @@
 The kernel's deadlock freedom rests on two properties of the ordered item
 list: every item appears exactly once, and every item an item waits for
 comes earlier in the list (statistics of a request < its decide < its pass-2
-items < its pick).  A small C++ driver compiled with g++ enumerates the list
+items < its pick; the statistics items that write full rows also wait for
+later ones of their row, but only for a bounded time, and end without them).
+A small C++ driver compiled with g++ enumerates the list
 for many shapes and these tests check both properties."""
 
 import os
