@@ -315,7 +315,6 @@ static int fuse_verify_impl(const void* t, const void* a, const void* b, int dty
   A.dec = (uint64_t*)(ws + L.off_dec);
   A.rec2 = (uint64_t*)(ws + L.off_rec2);
   A.err = (uint32_t*)(ws + L.off_err);
-  A.full_late = (uint64_t*)(ws + L.off_err + 8);
   A.stream_bytes = (unsigned long long)B * (K + 1) * (unsigned long long)V * (dtype == ASYMSPEC_BF16 ? 2ull : 4ull);
   A.B = B; A.K = K; A.V = V; A.S = L.S;
   A.beta = params->beta; A.gamma = params->gamma; A.gate_mode = params->gate_mode;

@@ -128,8 +128,7 @@ struct KArgs {
   int32_t* acc_out; int32_t* next_out; float* flp_out; float* gate_out;
   float* full;        // full log-probability rows written by the statistics items
   uint64_t* rec1; uint64_t* dec; uint64_t* rec2;
-  uint32_t* err;
-  uint64_t* full_late;   // slot: some item of this call left full rows unwritten
+  uint32_t* err;      // timeout counter; the slot full_late lies 8 bytes behind it
   unsigned long long stream_bytes;   // bytes of each logit array
   int B, K, V, S;
   int P2;             // pass-2 items per chunk
@@ -153,6 +152,8 @@ struct KArgs {
 #endif
 };
 
+// Slot that says that some item of this call left full rows unwritten.
+DEV uint64_t* full_late(const KArgs& A) { return reinterpret_cast<uint64_t*>(A.err) + 1; }
 // Decision header of a request, and decision block of its row i.
 DEV uint64_t* dec_hdr(const KArgs& A, int req) {
   return A.dec + (size_t)req * (kDecHdr + (size_t)(A.K + 1) * kDecRow);

@@ -41,7 +41,7 @@ __global__ __launch_bounds__(kThreads) void dump_kernel(KArgs A, float* out) {
 // grid that ends at one word when nothing is left, as in nearly every call.
 template <int DT, int DM>
 __global__ __launch_bounds__(kThreads) void full_rest_kernel(KArgs A) {
-  if (!tag_ok(*A.full_late, A.epoch)) return;
+  if (!tag_ok(*full_late(A), A.epoch)) return;
   const int S = A.S, nrow = A.K + 1;
   const long long nblk = (long long)A.B * nrow * S;
   for (long long b = blockIdx.x; b < nblk; b += gridDim.x) {

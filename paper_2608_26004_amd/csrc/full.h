@@ -70,7 +70,7 @@ struct FullPoll {
     const int reps = 1 << (n < kPollMaxShift ? n : kPollMaxShift);
     for (int i = 0; i < reps; ++i) __builtin_amdgcn_s_sleep(2);
     ++n;
-    if (tag_ok(ld_tag(A.full_late), A.epoch)) return false;
+    if (tag_ok(ld_tag(full_late(A)), A.epoch)) return false;
     const uint64_t most = A.poll_ticks < kFullTicks ? A.poll_ticks : kFullTicks;
     return __builtin_amdgcn_s_memrealtime() - t0 <= most;
   }
@@ -121,7 +121,7 @@ DEV bool full_norm(const KArgs& A, const RowGeo& g, Smem& sm, double& l2) {
       sm.flags[0] = in ? 1 : 0;
       if (!in) {
         st_tag(dec_hdr(A, g.req) + H_FULL, 1u, A.epoch);
-        st_tag(A.full_late, 1u, A.epoch);
+        st_tag(full_late(A), 1u, A.epoch);
       }
     }
   }
