@@ -4,7 +4,7 @@
 //
 // What bounds a mapped row is its gathers: a random 2-byte read from a row of
 // drafter logits moves a 128-byte line.  So a drafter row is cut into tiles of
-// kXTile logits, a tile of a and b is read once, contiguously, into LDS as
+// XTile::kN logits, a tile of a and b is read once, contiguously, into LDS as
 // (a, b) pairs, and the random half of every access is an LDS read.  The shared
 // tokens that map into a tile form the tile's list, in ascending verifier order,
 // so t is read nearly in order as well.  The lists are rebuilt from the map for
@@ -24,9 +24,8 @@
 // with one batch's gathers of t in flight while the batch before is reduced,
 // 311 us now; element-wise gathers from global memory, with a and b in drafter
 // order and t through the inverse map, took 1070 us.  What is left is bound by
-// the address unit (profiles/fuse_verify_xvocab_B128_K6_V151936_Vd128256_bf16.md):
-// in the statistics, two thirds of the call, it is 65% busy and the VALU 53%, with
-// 90 M cache accesses, about 50 per 64-lane gather of t.
+// the address unit: in the statistics, two thirds of the call, it is 65% busy and
+// the VALU 53%, with 90 M cache accesses, about 50 per 64-lane gather of t.
 
 #ifndef ASYMSPEC_XVOCAB_H_
 #define ASYMSPEC_XVOCAB_H_
